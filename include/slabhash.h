@@ -245,6 +245,27 @@ sh_status_t sh_delete(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint8_t
 sh_status_t sh_search(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_t *d_vals_out,
                       uint8_t *d_found, void *stream);
 
+/* The bulk form of sh_search and sh_insert (and sh_build), for batches with several operations
+   per bucket: the batch is split by bucket range in a caller-owned device workspace, so that a
+   slab is read once per batch and its new pairs are written together. Results, statuses, errors
+   and the rules for concurrent calls are those of sh_search and sh_insert; while a bulk insert
+   writes a slab, other inserts into that slab read it again until it is done.
+   sh_bulk_bytes gives the workspace (256-byte aligned) that a call of n operations of `kind`
+   (SH_OP_SEARCH or SH_OP_INSERT) on `stream` needs now, or 0 where the plain form serves it:
+   small batches, fewer than four operations per bucket, inserts that the base slabs would have no
+   room for, tables with flags (inserts), tables with a launch shape set by sh_set_launch, and
+   streams that are being captured. The calls themselves take the plain form where there is no
+   bulk form or the workspace is missing (NULL) or too small. The workspace belongs to one call:
+   its contents need not be set before and mean nothing after, and calls that may overlap need one
+   each. It is at most 1.1 GB: longer batches are taken in pieces of 2^26. */
+size_t sh_bulk_bytes(const sh_table_t *t, int kind, uint64_t n, void *stream);
+sh_status_t sh_search_bulk(sh_table_t *t, const uint32_t *d_keys, uint64_t n,
+                           uint32_t *d_vals_out, uint8_t *d_found, void *d_work,
+                           size_t work_bytes, void *stream);
+sh_status_t sh_insert_bulk(sh_table_t *t, const uint32_t *d_keys, const uint32_t *d_vals,
+                           uint64_t n, uint8_t *d_status, void *d_work, size_t work_bytes,
+                           void *stream);
+
 /* Concurrent mixed batch ("Concurrent benchmarks"): d_ops[i] in {SH_OP_SEARCH, SH_OP_INSERT,
    SH_OP_DELETE} applies to d_keys[i] (and d_vals_in[i] for inserts); all ops of the batch run
    concurrently and the outcome is linearizable. d_vals_out[i] gets the search result

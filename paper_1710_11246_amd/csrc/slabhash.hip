@@ -19,6 +19,7 @@
 // ballots and lane reads; the slab loads for all of a chunk's operations are issued ahead of the
 // decisions and the resulting swaps are committed together (see ops_kernel).
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
@@ -38,6 +39,9 @@ namespace {
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 constexpr uint64_t kEmptyPair = ~0ull;
 constexpr uint64_t kTombPair = 0x00000000FFFFFFFFull; // key half all ones, value half 0
+// A base slab's first empty slot while a bulk insert writes the slots after it (unique-key pair
+// tables): inserts that meet it read the slab again.
+constexpr uint64_t kLockPair = 0xFFFFFFFEFFFFFFFFull;
 constexpr uint32_t kTombKey = 0xFFFFFFFEu;            // a deleted entry of a key-only slab
 constexpr uint32_t kKeyEntries = 62;                  // keys per key-only slab
 constexpr uint64_t kSlotMask = 0x7FFFFFFFull;         // slots 0..30 of a half wavefront
@@ -97,6 +101,7 @@ struct View {
     uint32_t B, a, b, pool_slabs, nblk;
     uint32_t nsuper, total_blocks; // super blocks registered, allocator blocks in all of them
     uint32_t mode; // SH_TABLE_DUPLICATES | SH_TABLE_KEYS_ONLY bits of the table's flags
+    uint32_t bmagic; // for bucket numbers without a division (div_magic)
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -606,7 +611,10 @@ __device__ __forceinline__ uint64_t decide_kv(const uint64_t (&pre)[NQ], uint64_
         kmv = wl(kmv, 2 * q, (uint32_t)km);
         kmv = wl(kmv, 2 * q + 1, (uint32_t)(km >> 32));
         if constexpr (kHasIns) {
-            const uint64_t em = ballot(w == kEmptyPair);
+            // a locked slot counts as the empty slot that it was: the swap then meets the lock
+            const uint64_t em = ballot(Dup ? w == kEmptyPair
+                                           : (uint32_t)w == kEmpty &&
+                                                 (uint32_t)(w >> 32) >= (uint32_t)(kLockPair >> 32));
             emv = wl(emv, 2 * q, (uint32_t)em);
             emv = wl(emv, 2 * q + 1, (uint32_t)(em >> 32));
         }
@@ -649,12 +657,12 @@ __device__ __forceinline__ uint64_t decide_kv(const uint64_t (&pre)[NQ], uint64_
     return ((uint64_t)((code << 8) | tslot) << 32) | payload;
 }
 
-// One chunk of up to 2 NQ ops (lane l < count holds op base + l, with inputs `c`) on table T,
+// One chunk of up to 2 NQ ops (lane l < count holds op i, with inputs `c`) on table T,
 // processed in rounds until every op has finished (see the description above). NQ is the
 // number of op pairs, and so the length of each round's straight run of loads.
 template <int K, bool Dup, bool KO, int NQ = 32>
 __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, ChunkIn c,
-                          uint32_t *__restrict__ vout, uint8_t *__restrict__ sout, uint64_t base,
+                          uint32_t *__restrict__ vout, uint8_t *__restrict__ sout, uint64_t i,
                           uint32_t count, uint32_t flags)
 {
     constexpr bool kCoherent = (K != kSearch);
@@ -666,7 +674,6 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
     const bool is31 = slot == 31;
     const uint32_t below = (1u << slot) - 1u; // slots of my half below mine
     const uint32_t hshift = lane & 32;
-    const uint64_t i = base + lane;
     const bool in = lane < count;
     const uint32_t key = c.key, val = c.val, op = c.op;
     // key-only slabs reserve a second key, the deleted-entry marker
@@ -906,6 +913,10 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                     // return; at most the 31 slots of this slab. (With duplicates, empty slots
                     // need not be a suffix, so a lost insert re-reads its slab next round.)
                     for (;;) {
+                        if (old == kLockPair) {
+                            lost = true; // a bulk insert holds the slab: read it again
+                            break;
+                        }
                         if ((uint32_t)old == key) { // the same key was inserted: replace it
                             expect = old;
                             old = cas64(slab + cslot, expect, desired);
@@ -1079,7 +1090,8 @@ __global__ __launch_bounds__(kBlock) void ops_kernel(View T, const uint8_t *__re
         const uint64_t base = c * C;
         const uint32_t count = (uint32_t)((n - base < C) ? n - base : C);
         const ChunkIn cur = load_chunk<K, KO>(ops, keys, vals, base, count);
-        run_chunk<K, Dup, KO, NQ>(T, al, cnt, lds[wl_], cur, vout, sout, base, count, flags);
+        run_chunk<K, Dup, KO, NQ>(T, al, cnt, lds[wl_], cur, vout, sout, base + lane_id(),
+                                  count, flags);
     }
     if (flags & kFlagCounters)
         flush_counters(T, cnt, al, wave);
@@ -1176,8 +1188,8 @@ __global__ __launch_bounds__(kBlock) void multi_kernel(const View *__restrict__ 
         }
         run_chunk<kMixed, false, false, NQ>(
             Tv, al, cnt, lds[wl_],
-            load_chunk<kMixed, false>(ops, keys, vals, base, (uint32_t)count), vout, sout, base,
-            (uint32_t)count, flags);
+            load_chunk<kMixed, false>(ops, keys, vals, base, (uint32_t)count), vout, sout,
+            base + lane_id(), (uint32_t)count, flags);
     }
     if ((flags & kFlagCounters) && cur_t != kEmpty)
         flush_counters(dir[cur_t], cnt, al, wave);
@@ -1756,6 +1768,8 @@ __global__ __launch_bounds__(kBlock) void reset_kernel(View T, uint4 *store, siz
     }
 }
 
+#include "bulk.hpp"
+
 } // namespace
 
 // ---------------------------------------------------------------------------------------------
@@ -1775,6 +1789,7 @@ struct sh_table {
     struct sh_multi *owner; // that object, and this table's index in it
     uint32_t index;
     uint64_t super_slabs; // slabs of the super blocks registered beyond super block 0
+    uint64_t taken;       // inserts since the last reset: a bound on the slots in use
 };
 
 struct sh_multi {
@@ -1813,6 +1828,8 @@ bool layout_of(const sh_params_t *p, Layout *L)
     L->total = L->bitmap + (size_t)(p->pool_slabs / SH_BLOCK_SLABS) * 256;
     return true;
 }
+
+size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 hipStream_t S(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
@@ -2011,9 +2028,170 @@ sh_status_t launch_ops(sh_table *t, const uint8_t *ops, const uint32_t *keys,
         launch_wpc(t->waves_per_cu, default_shape(t, K).waves_per_cu, reinterpret_cast<const void *>(fn));
     const dim3 grid(grid_for(t, n, C, wpc));
     const uint32_t seq = next_seq(&t->seq);
+    if constexpr (K == kInsert || K == kMixed)
+        __atomic_fetch_add(&t->taken, n, __ATOMIC_RELAXED);
     hipLaunchKernelGGL(fn, grid, dim3(kBlock), 0, S(stream), t->v, ops, keys, vals, n, vout, sout,
                        seq, t->flags);
     return check_launch();
+}
+
+// The bulk form's plan for one call: how a batch of n operations on table t is cut into tiles
+// and parts, and where its arrays lie in the workspace.
+struct BulkPlan {
+    uint32_t rows;  // operations per thread of a split workgroup (its tile / 1024)
+    uint32_t waves; // wavefronts of a part's workgroup
+    uint64_t chunk; // operations per pass over the kernels
+    Bulk a;
+    size_t starts, key, val, place, flag, later, total; // byte offsets
+    size_t split_lds, part_lds, merge_lds;
+};
+
+constexpr size_t kLdsBytes = 160 * 1024;
+constexpr uint64_t kBulkSearches = 1u << 20, kBulkInserts = 1u << 19; // the smallest batches
+constexpr uint32_t kBulkBuckets = 1u << 12; // and tables
+constexpr uint32_t kBulkFill = 26; // slots taken per base slab after an insert call, at most
+
+// Whether the call takes the bulk form, and how. A part of about 2048 operations keeps a
+// workgroup of 8 wavefronts busy while three of them share a compute unit's LDS (2^22 searches of
+// 2^22 keys: 79, 62, 64 and 71 us with 1024, 2048, 2560 and 4096 parts); batches with more such
+// parts than a tile can count take larger ones, 16 wavefronts each (2^26 searches: 1.54 ms
+// against 1.92 ms with 8). Tiles grow with the batch: a tile per compute unit at least, and runs
+// of several operations per part.
+bool bulk_plan(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
+{
+    const bool ins = kind == kInsert;
+    const uint32_t B = t->v.B;
+    const bool ko = (t->v.mode & SH_TABLE_KEYS_ONLY) != 0;
+    if ((kind != kSearch && kind != kInsert) || (ins && t->v.mode) || t->flags ||
+        t->waves_per_cu || t->ops_per_wave)
+        return false;
+    P->chunk = n < (1ull << 26) ? n : (1ull << 26);
+    const uint64_t m = P->chunk;
+    if (m < (ins ? kBulkInserts : kBulkSearches) || m / 4 < B || B < kBulkBuckets)
+        return false;
+    // inserts that the base slabs have no room for are made the plain way, after the others:
+    // nothing is gained where they are many
+    if (ins && __atomic_load_n(&t->taken, __ATOMIC_RELAXED) + n > (uint64_t)B * kBulkFill)
+        return false;
+    P->rows = m <= (3u << 19) ? 4 : m <= (1u << 23) ? 16 : 32;
+    Bulk &A = P->a;
+    A.tile = P->rows * kSplitThreads;
+    A.tiles = (uint32_t)((m + A.tile - 1) / A.tile);
+    P->waves = 8;
+    uint64_t parts = (m + 2047) / 2048;
+    if (parts < B / 160)
+        parts = B / 160; // few operations per bucket: the slabs bound the part
+    if (parts > kMaxParts) {
+        P->waves = 16;
+        parts = (m + 6553) / 6554;
+        if (parts < B / 400)
+            parts = B / 400;
+    }
+    const uint64_t cus = (uint64_t)t->num_cu;
+    parts = (parts + cus - 1) / cus * cus;
+    if (parts > kMaxParts)
+        return false;
+    const uint32_t span = (uint32_t)((B + parts - 1) / parts);
+    A.span = span;
+    A.span_magic = magic_for(span);
+    A.parts = (B + span - 1) / span;
+    if (A.parts > kMaxParts || A.tiles > kMaxTiles || span > kMaxSpan)
+        return false;
+    A.row = split_row_words(A.parts);
+    // a part's share varies as a sum of independent operations does
+    const double avg = (double)m / A.parts;
+    A.queue = (uint32_t)(avg + 6 * sqrt(avg) + 64) & ~3u;
+    if (A.queue > 32 * P->waves * 64)
+        A.queue = 32 * P->waves * 64;
+    A.hot = ins ? 0xFFFFu : 3 * (A.tile / A.parts) + 16;
+    P->split_lds = ((size_t)A.tile + A.row + kSplitThreads / 64 + 1) * 4;
+    const size_t runs = 8 * (size_t)A.tiles + 4 + 4 * P->waves;
+    P->part_lds = ins ? (size_t)span * kInsRowBytes + 8 + runs + 4 * (size_t)A.queue
+                      : (size_t)span * (kRowWords * 8 + (ko ? 64 : 32)) + 8 + runs + 4 +
+                            64 * P->waves + 6 * (size_t)A.queue;
+    P->merge_lds = (size_t)A.tile * (ins ? 1 : 5);
+    if (P->split_lds > kLdsBytes || P->part_lds > kLdsBytes || P->merge_lds > kLdsBytes)
+        return false;
+    const size_t slots = (size_t)A.tiles * A.tile;
+    size_t off = 256;
+    auto take = [&off](size_t bytes) {
+        const size_t at = off;
+        off = round256(off + bytes);
+        return at;
+    };
+    P->starts = take((size_t)A.tiles * A.row * 4);
+    P->key = take(slots * 4);
+    P->place = take(slots * 2);
+    P->flag = take(slots);
+    P->val = ins ? take(slots * 4) : 0;
+    P->later = ins ? take(slots * 4) : 0;
+    P->total = off;
+    return true;
+}
+
+// Dynamic LDS beyond 64 KB has to be asked for.
+template <typename F>
+bool allow_lds(F fn, size_t bytes)
+{
+    return bytes <= 64 * 1024 ||
+           hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)bytes) == hipSuccess;
+}
+
+template <bool Vals>
+auto split_fn(uint32_t rows)
+{
+    return rows == 32 ? split_kernel<32, Vals> : rows == 16 ? split_kernel<16, Vals>
+                                                            : split_kernel<4, Vals>;
+}
+
+// The bulk form of one search (vals null) or insert call.
+sh_status_t launch_bulk(sh_table *t, const BulkPlan &P, const uint32_t *keys, const uint32_t *vals,
+                        uint64_t n, uint32_t *vout, uint8_t *sout, char *ws, void *stream)
+{
+    const bool ko = (t->v.mode & SH_TABLE_KEYS_ONLY) != 0, ins = vals != nullptr;
+    Bulk A = P.a;
+    A.later_count = reinterpret_cast<uint32_t *>(ws);
+    A.starts = reinterpret_cast<uint16_t *>(ws + P.starts);
+    A.key = reinterpret_cast<uint32_t *>(ws + P.key);
+    A.val = reinterpret_cast<uint32_t *>(ws + P.val);
+    A.place = reinterpret_cast<uint16_t *>(ws + P.place);
+    A.flag = reinterpret_cast<uint8_t *>(ws + P.flag);
+    A.later = reinterpret_cast<uint32_t *>(ws + P.later);
+    const auto split = ins ? split_fn<true>(P.rows) : split_fn<false>(P.rows);
+    const auto merge = P.rows == 32   ? merge_kernel<32>
+                       : P.rows == 16 ? merge_kernel<16>
+                                      : merge_kernel<4>;
+    const bool wide = P.waves == 16;
+    const auto part = ins  ? (wide ? insert_kernel<16> : insert_kernel<8>)
+                      : ko ? (wide ? probe_kernel<true, 16> : probe_kernel<true, 8>)
+                           : (wide ? probe_kernel<false, 16> : probe_kernel<false, 8>);
+    if (ins)
+        __atomic_fetch_add(&t->taken, n, __ATOMIC_RELAXED);
+    if (!allow_lds(split, P.split_lds) || !allow_lds(merge, P.merge_lds) ||
+        !allow_lds(part, P.part_lds))
+        return SH_EHIP;
+    for (uint64_t o = 0; o < n; o += P.chunk) {
+        const uint64_t m = n - o < P.chunk ? n - o : P.chunk;
+        A.tiles = (uint32_t)((m + A.tile - 1) / A.tile);
+        hipLaunchKernelGGL(split, dim3(A.tiles), dim3(kSplitThreads), P.split_lds, S(stream), t->v,
+                           A, keys + o, ins ? vals + o : nullptr, m, ko ? kTombKey : kEmpty);
+        hipLaunchKernelGGL(part, dim3((A.parts + 7) / 8 * 8), dim3(P.waves * 64), P.part_lds,
+                           S(stream), t->v, A);
+        if (ins) {
+            const void *fn = reinterpret_cast<const void *>(later_kernel<8>);
+            const uint32_t wpc = launch_wpc(0, default_shape(t, kInsert).waves_per_cu, fn);
+            hipLaunchKernelGGL(later_kernel<8>, dim3(grid_for(t, m, 16, wpc)), dim3(kBlock), 0,
+                               S(stream), t->v, A, next_seq(&t->seq));
+        }
+        if (vout || sout)
+            hipLaunchKernelGGL(merge, dim3(A.tiles), dim3(kSplitThreads), P.merge_lds, S(stream),
+                               A, m, vout ? vout + o : nullptr, sout ? sout + o : nullptr);
+        if (check_launch() != SH_OK)
+            return SH_EHIP;
+    }
+    return SH_OK;
 }
 
 sh_status_t walk(sh_table *t, uint32_t *dbkt, uint32_t *dkey, uint32_t *dval, uint64_t cap,
@@ -2091,10 +2269,9 @@ void bind_table(sh_table *t, const sh_params_t *p, char *storage, size_t bytes, 
     t->v.nsuper = 1;
     t->v.total_blocks = t->v.nblk;
     t->v.mode = p->flags & (SH_TABLE_DUPLICATES | SH_TABLE_KEYS_ONLY);
+    t->v.bmagic = magic_for(p->num_buckets);
     t->super_slabs = 0;
 }
-
-size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Directory first, then each table's storage, all 256-byte aligned. offs[t] (if given) gets the
 // byte offset of table t. Returns 0 for invalid input.
@@ -2204,6 +2381,7 @@ sh_status_t sh_reset(sh_table_t *t, void *stream)
 {
     if (!t)
         return SH_EINVAL;
+    __atomic_store_n(&t->taken, 0, __ATOMIC_RELAXED);
     Layout L;
     layout_of(&t->p, &L);
     const size_t hdr16 = kHeaderBytes / 16;
@@ -2447,6 +2625,46 @@ sh_status_t sh_search(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_
     if (n && !d_vals_out)
         return SH_EINVAL;
     return launch_ops<kSearch>(t, nullptr, d_keys, nullptr, n, d_vals_out, d_found, stream);
+}
+
+size_t sh_bulk_bytes(const sh_table_t *t, int kind, uint64_t n, void *stream)
+{
+    BulkPlan P;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!t || n == 0 || n >= (1ull << 32) || !bulk_plan(t, kind, n, &P))
+        return 0;
+    if (stream && hipStreamIsCapturing(S(stream), &st) != hipSuccess) {
+        (void)hipGetLastError(); // left for the call itself to find
+        return 0;
+    }
+    return st == hipStreamCaptureStatusNone ? P.total : 0;
+}
+
+sh_status_t sh_search_bulk(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_t *d_vals_out,
+                           uint8_t *d_found, void *d_work, size_t work_bytes, void *stream)
+{
+    BulkPlan P;
+    if (reinterpret_cast<uintptr_t>(d_work) & 255u)
+        return SH_EINVAL;
+    if (!t || !d_work || n == 0 || n >= (1ull << 32) || !d_keys || !d_vals_out ||
+        !bulk_plan(t, kSearch, n, &P) || work_bytes < P.total)
+        return sh_search(t, d_keys, n, d_vals_out, d_found, stream);
+    return launch_bulk(t, P, d_keys, nullptr, n, d_vals_out, d_found, static_cast<char *>(d_work),
+                       stream);
+}
+
+sh_status_t sh_insert_bulk(sh_table_t *t, const uint32_t *d_keys, const uint32_t *d_vals,
+                           uint64_t n, uint8_t *d_status, void *d_work, size_t work_bytes,
+                           void *stream)
+{
+    BulkPlan P;
+    if (reinterpret_cast<uintptr_t>(d_work) & 255u)
+        return SH_EINVAL;
+    if (!t || !d_work || n == 0 || n >= (1ull << 32) || !d_keys || !d_vals ||
+        !bulk_plan(t, kInsert, n, &P) || work_bytes < P.total)
+        return sh_insert(t, d_keys, d_vals, n, d_status, stream);
+    return launch_bulk(t, P, d_keys, d_vals, n, nullptr, d_status, static_cast<char *>(d_work),
+                       stream);
 }
 
 sh_status_t sh_mixed(sh_table_t *t, const uint8_t *d_ops, const uint32_t *d_keys,

@@ -13,6 +13,7 @@ from __future__ import annotations
 import ctypes
 import os
 import re
+import threading
 
 import numpy as np
 import torch
@@ -98,6 +99,9 @@ _SIGS = {
     "sh_insert": ([_P, _P, _P, _U64, _P, _P], ctypes.c_int),
     "sh_delete": ([_P, _P, _U64, _P, _P], ctypes.c_int),
     "sh_search": ([_P, _P, _U64, _P, _P, _P], ctypes.c_int),
+    "sh_bulk_bytes": ([_P, ctypes.c_int, _U64, _P], _SZ),
+    "sh_search_bulk": ([_P, _P, _U64, _P, _P, _P, _SZ, _P], ctypes.c_int),
+    "sh_insert_bulk": ([_P, _P, _P, _U64, _P, _P, _SZ, _P], ctypes.c_int),
     "sh_mixed": ([_P, _P, _P, _P, _U64, _P, _P, _P], ctypes.c_int),
     "sh_stats": ([_P, _P, _P], ctypes.c_int),
     "sh_dump": ([_P, _P, _P, _P, _U64, _P, _P, _P, _P], ctypes.c_int),
@@ -160,6 +164,40 @@ def _stream(stream) -> int:
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
+
+
+# sh_capture_begin calls of this thread that sh_capture_end has not ended
+_capturing = threading.local()
+
+#: No batch below this takes the bulk form (the library's own lines lie at or above it).
+_BULK_MIN = 1 << 19
+
+
+def sh_bulk_bytes(t, kind: int, n: int, stream=None) -> int:
+    return int(lib().sh_bulk_bytes(t, int(kind), int(n), _stream(stream)))
+
+
+def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
+    """The workspace of a call's bulk form, or None for the plain form: torch memory of the
+    stream that the call runs on, so that it returns to that stream's pool when the call has
+    been enqueued. A stream that torch does not own, a capture in progress and a device without
+    room take the plain form."""
+    n = keys.numel()
+    if n < _BULK_MIN or getattr(_capturing, "depth", 0):
+        return None
+    cur = torch.cuda.current_stream()
+    if stream is None or _stream(stream) == cur.cuda_stream:
+        stream = cur
+    elif type(stream) is not torch.cuda.Stream:
+        return None
+    nbytes = sh_bulk_bytes(t, kind, n, stream)
+    if nbytes == 0:
+        return None
+    try:
+        with torch.cuda.stream(stream):
+            return torch.empty(nbytes, dtype=torch.uint8, device=keys.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
 
 
 _U32_TYPES = (torch.int32,) + ((torch.uint32,) if hasattr(torch, "uint32") else ())
@@ -265,19 +303,25 @@ def sh_launch_shape(t, kind: int, n: int) -> tuple[int, int]:
     return int(w.value), int(c.value)
 
 
+def _insert(fn: str, t, keys, vals, status, stream) -> None:
+    n = keys.numel()
+    k, v = _dev(keys, "keys", _U32_TYPES), _dev(vals, "vals", _U32_TYPES, n, True)
+    st = _dev(status, "status", (torch.uint8,), n, True)
+    work = _bulk_work(t, SH_OP_INSERT, keys, stream)
+    if work is not None:
+        _check(fn, lib().sh_insert_bulk(t, k, v, n, st, work.data_ptr(), work.numel(),
+                                        _stream(stream)))
+        return
+    _check(fn, getattr(lib(), fn)(t, k, v, n, st, _stream(stream)))
+
+
 def sh_build(t, keys, vals, status=None, stream=None) -> None:
     """vals may be None for a key-only table (the library rejects it for key-value tables)."""
-    n = keys.numel()
-    _check("sh_build", lib().sh_build(
-        t, _dev(keys, "keys", _U32_TYPES), _dev(vals, "vals", _U32_TYPES, n, True), n,
-        _dev(status, "status", (torch.uint8,), n, True), _stream(stream)))
+    _insert("sh_build", t, keys, vals, status, stream)
 
 
 def sh_insert(t, keys, vals, status=None, stream=None) -> None:
-    n = keys.numel()
-    _check("sh_insert", lib().sh_insert(
-        t, _dev(keys, "keys", _U32_TYPES), _dev(vals, "vals", _U32_TYPES, n, True), n,
-        _dev(status, "status", (torch.uint8,), n, True), _stream(stream)))
+    _insert("sh_insert", t, keys, vals, status, stream)
 
 
 def sh_delete(t, keys, status=None, stream=None) -> None:
@@ -289,9 +333,14 @@ def sh_delete(t, keys, status=None, stream=None) -> None:
 
 def sh_search(t, keys, vals_out, found=None, stream=None) -> None:
     n = keys.numel()
-    _check("sh_search", lib().sh_search(
-        t, _dev(keys, "keys", _U32_TYPES), n, _dev(vals_out, "vals_out", _U32_TYPES, n),
-        _dev(found, "found", (torch.uint8,), n, True), _stream(stream)))
+    k, v = _dev(keys, "keys", _U32_TYPES), _dev(vals_out, "vals_out", _U32_TYPES, n)
+    f = _dev(found, "found", (torch.uint8,), n, True)
+    work = _bulk_work(t, SH_OP_SEARCH, keys, stream)
+    if work is not None:
+        _check("sh_search", lib().sh_search_bulk(t, k, n, v, f, work.data_ptr(), work.numel(),
+                                                 _stream(stream)))
+        return
+    _check("sh_search", lib().sh_search(t, k, n, v, f, _stream(stream)))
 
 
 def sh_mixed(t, ops, keys, vals_in, vals_out, status, stream=None) -> None:
@@ -397,11 +446,13 @@ def sh_multi_graph(m, desc, nb, ops, keys, vals_in, vals_out, status) -> ctypes.
 def sh_capture_begin(stream) -> None:
     """Start capturing the work later calls enqueue on `stream` (a non-default stream)."""
     _check("sh_capture_begin", lib().sh_capture_begin(_stream(stream)))
+    _capturing.depth = getattr(_capturing, "depth", 0) + 1
 
 
 def sh_capture_end(stream) -> ctypes.c_void_p:
     """Finish the capture on `stream`; returns the graph (replay with sh_graph_launch)."""
     out = ctypes.c_void_p()
+    _capturing.depth = max(0, getattr(_capturing, "depth", 0) - 1)
     _check("sh_capture_end", lib().sh_capture_end(_stream(stream), ctypes.byref(out)))
     return out
 
