@@ -1727,10 +1727,15 @@ __global__ void set_super_kernel(SuperDesc *dir, uint32_t sb, uint64_t *pool, ui
 // super-block directory, which stays registered), filling the base slabs with ones, and filling
 // only the pool slabs the bitmaps mark allocated, in every super block, before zeroing the
 // bitmaps. Blocks [fill start, grid end) do the header and base slabs (16-byte stores,
-// grid-stride over them); the others take one bitmap row (2048 pool slabs) per wavefront,
-// grid-stride over the rows of all super blocks.
+// grid-stride over them); the others take eight words of a bitmap row (256 pool slabs) per
+// wavefront, grid-stride over the rows of all super blocks.
 // The bitmap walkers take the first blocks, so they are dispatched before the fill blocks
 // occupy the CUs; their dependent bitmap loads then overlap the fill instead of trailing it.
+// The slabs in use sit in few rows, those the inserting wavefronts started in: a wavefront per
+// row, a slab a store, made the fullest row the kernel's time (2^22 keys at utilisation 0.65, about
+// 13,000 slabs in use: 110 us, and 12 us as it is; 2^22 keys at 0.8, 110,000 slabs: 370 us more).
+constexpr uint32_t kResetWords = 8;
+
 __global__ __launch_bounds__(kBlock) void reset_kernel(View T, uint4 *store, size_t hdr16,
                                                        size_t base16, uint32_t pool_blocks)
 {
@@ -1747,24 +1752,36 @@ __global__ __launch_bounds__(kBlock) void reset_kernel(View T, uint4 *store, siz
         }
         return;
     }
+    // Each wavefront takes eight words of a bitmap row (kResetWords), 256 slabs. A slab is 16 lanes
+    // of 16 bytes: four slabs a store.
     const uint32_t lane = lane_id();
     const uint32_t wave = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     const uint32_t nwaves = pool_blocks * kWavesPerBlock;
-    // allocator blocks of every registered super block
-    for (uint32_t r = wave; r < T.total_blocks; r += nwaves) {
+    constexpr uint32_t kPerRow = 64 / kResetWords;
+    for (uint64_t g = wave; g < (uint64_t)T.total_blocks * kPerRow; g += nwaves) {
         uint32_t *row, code;
-        block_ref(T, r, row, code);
-        uint32_t word = row[lane]; // slabs code + 32 lane + bit
-        // the wavefront writes each allocated slab whole: 64 lanes x 4 bytes
-        for (uint64_t m = ballot(word != 0); m; m = ballot(word != 0)) {
-            const uint32_t j = ffs0(m);
-            const uint32_t bit = (uint32_t)__builtin_ctz(rl(word, j));
-            uint32_t *sl = reinterpret_cast<uint32_t *>(pool_slab(T, code + j * 32 + bit));
-            sl[lane] = kEmpty;
-            if (lane == j)
-                word &= word - 1u; // that slab is done
+        block_ref(T, (uint32_t)(g / kPerRow), row, code);
+        const uint32_t j = (uint32_t)(g % kPerRow) * kResetWords;
+        const uint32_t word = lane < kResetWords ? row[j + lane] : 0u;
+        // the slabs in use, four at a time: lanes 16 i .. 16 i + 15 write the i-th of them
+        for (uint64_t any = ballot(word != 0); any; any &= any - 1) {
+            const uint32_t l = ffs0(any);
+            const uint32_t base = code + (j + l) * 32;
+            for (uint32_t m = rl(word, l); m;) {
+                uint32_t mine = 32;
+#pragma unroll
+                for (uint32_t i = 0; i < 4; ++i) {
+                    if (m && (lane >> 4) == i)
+                        mine = (uint32_t)__builtin_ctz(m);
+                    m &= m - 1u; // (0 stays 0)
+                }
+                if (mine < 32)
+                    reinterpret_cast<uint4 *>(pool_slab(T, base + mine))[lane & 15u] =
+                        make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
+            }
         }
-        row[lane] = 0u;
+        if (word)
+            row[j + lane] = 0u;
     }
 }
 
@@ -2390,9 +2407,9 @@ sh_status_t sh_reset(sh_table_t *t, void *stream)
     const size_t cap = (size_t)t->num_cu * 8;
     if (fill > cap)
         fill = cap;
-    // one wavefront per bitmap row, at most the rows of every super block
-    const size_t rows = t->v.total_blocks;
-    size_t pool_blocks = (rows + kWavesPerBlock - 1) / kWavesPerBlock;
+    // one wavefront per eight words of the bitmap rows of every super block
+    const size_t groups = (size_t)t->v.total_blocks * (64 / kResetWords);
+    size_t pool_blocks = (groups + kWavesPerBlock - 1) / kWavesPerBlock;
     if (pool_blocks > cap)
         pool_blocks = cap;
     hipLaunchKernelGGL(reset_kernel, dim3((uint32_t)(fill + pool_blocks)), dim3(kBlock), 0,
