@@ -252,7 +252,7 @@ sh_status_t sh_search(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_
    writes a slab, other inserts into that slab read it again until it is done.
    sh_bulk_bytes gives the workspace (256-byte aligned) that a call of n operations of `kind`
    (SH_OP_SEARCH or SH_OP_INSERT) on `stream` needs now, or 0 where the plain form serves it:
-   small batches, fewer than four operations per bucket, inserts that the base slabs would have no
+   small batches, fewer than six operations per bucket, inserts that the base slabs would have no
    room for, tables with flags (inserts), tables with a launch shape set by sh_set_launch, and
    streams that are being captured. The calls themselves take the plain form where there is no
    bulk form or the workspace is missing (NULL) or too small. The workspace belongs to one call:

@@ -62,17 +62,21 @@ __device__ __forceinline__ uint32_t bucket_fast(const View &T, uint32_t k)
     return rem;
 }
 
-// Inclusive sum over the wavefront's lanes.
+// Inclusive sum over the wavefront's lanes: four shifts within rows of 16 lanes, then the sums of
+// the rows before (lane 15 of rows 0 and 2 to rows 1 and 3, lane 31 to rows 2 and 3).
+template <int Ctrl, int Rows>
+__device__ __forceinline__ uint32_t add_dpp(uint32_t x)
+{
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, Ctrl, Rows, 0xF, false);
+}
 __device__ __forceinline__ uint32_t wave_scan(uint32_t x)
 {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (uint32_t d = 1; d < 64; d <<= 1) {
-        const uint32_t t = (uint32_t)__shfl_up((int)x, d, 64);
-        if (lane >= d)
-            x += t;
-    }
-    return x;
+    x = add_dpp<0x111, 0xF>(x);
+    x = add_dpp<0x112, 0xF>(x);
+    x = add_dpp<0x114, 0xF>(x);
+    x = add_dpp<0x118, 0xF>(x);
+    x = add_dpp<0x142, 0xA>(x);
+    return add_dpp<0x143, 0xC>(x);
 }
 
 // Exclusive sum over the workgroup's threads (NW wavefronts); *total receives the sum. `tmp`
@@ -181,29 +185,43 @@ __global__ __launch_bounds__(kSplitThreads) void split_kernel(View T, Bulk A,
         for (uint32_t i = tid; i < kTable; i += kSplitThreads)
             tkey[i] = kEmpty;
         __syncthreads();
+        // (eight keys of a thread at a time, their swaps in flight together)
+        constexpr int kB = R < 8 ? R : 8;
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            if (index(j) < count && start[pr[j] >> 16] > A.hot && k[j] != kEmpty) {
-                inhot |= 1u << j;
-                first |= 1u << j;
-                uint32_t h = (k[j] * 0x9E3779B1u) >> (32 - kTableBits);
-                uint32_t at = kTable;
-                for (uint32_t d = 0; d < 8; ++d, h = (h + 1) & (kTable - 1)) {
-                    // a plain read first: most keys here find themselves without an atomic
-                    uint32_t old = *const_cast<volatile uint32_t *>(&tkey[h]);
-                    if (old == kEmpty)
-                        old = atomicCAS(&tkey[h], kEmpty, k[j]);
-                    if (old == kEmpty || old == k[j]) {
-                        at = h;
-                        if (old == k[j])
-                            first &= ~(1u << j);
-                        break;
-                    }
-                }
-                // the key's entry, in place of its rank; a key that found none is counted as
-                // if it were the only one
-                pr[j] = (pr[j] & 0xFFFF0000u) | at;
+        for (int j0 = 0; j0 < R; j0 += kB) {
+            uint32_t h[kB], old[kB], left = 0;
+#pragma unroll
+            for (int j = 0; j < kB; ++j) {
+                h[j] = (k[j0 + j] * 0x9E3779B1u) >> (32 - kTableBits);
+                if (index(j0 + j) < count && start[pr[j0 + j] >> 16] > A.hot)
+                    left |= 1u << j;
             }
+            inhot |= left << j0;
+            first |= left << j0;
+            for (uint32_t d = 0; d < 8 && left; ++d) {
+#pragma unroll
+                for (int j = 0; j < kB; ++j)
+                    if (((left >> j) & 1u) && k[j0 + j] != kEmpty) // (the empty entry's mark)
+                        old[j] = atomicCAS(&tkey[h[j]], kEmpty, k[j0 + j]);
+#pragma unroll
+                for (int j = 0; j < kB; ++j)
+                    if (((left >> j) & 1u) && k[j0 + j] != kEmpty) {
+                        if (old[j] == kEmpty || old[j] == k[j0 + j]) {
+                            left &= ~(1u << j);
+                            if (old[j] != kEmpty)
+                                first &= ~(1u << (j0 + j));
+                            // the key's entry, in place of its rank
+                            pr[j0 + j] = (pr[j0 + j] & 0xFFFF0000u) | h[j];
+                        } else {
+                            h[j] = (h[j] + 1) & (kTable - 1);
+                        }
+                    }
+            }
+            // a key that found no entry is counted as if it were the only one
+#pragma unroll
+            for (int j = 0; j < kB; ++j)
+                if ((left >> j) & 1u)
+                    pr[j0 + j] = (pr[j0 + j] & 0xFFFF0000u) | kTable;
         }
         __syncthreads();
         // the hot runs are counted again, without the repetitions
@@ -307,8 +325,27 @@ struct Runs {
     uint32_t *first, *shift;
 };
 
+// Writes the runs of the wavefront's lanes (operations lo .. hi - 1 of the queue come from `tile`):
+// each lane its own, the wavefront together the long ones.
+__device__ __forceinline__ void write_owner(uint16_t *owner, uint32_t lo, uint32_t hi, uint32_t tile)
+{
+    const bool is_long = hi > lo && hi - lo > 64u;
+    if (!is_long)
+        for (uint32_t q = lo; q < hi; ++q)
+            owner[q] = (uint16_t)tile;
+    for (uint64_t m = ballot(is_long); m; m &= m - 1) {
+        const uint32_t l = ffs0(m);
+        const uint32_t end = rl(hi, l), t = rl(tile, l);
+        for (uint32_t q = rl(lo, l) + lane_id(); q < end; q += 64)
+            owner[q] = (uint16_t)t;
+    }
+}
+
+// Reads the part's runs; returns the number of its operations. If one queue holds them all, their
+// owners are written too.
 template <int NW>
-__device__ __forceinline__ uint32_t load_runs(const Bulk &A, uint32_t part, Runs R, uint32_t *tmp)
+__device__ __forceinline__ uint32_t load_runs(const Bulk &A, uint32_t part, Runs R, uint32_t *tmp,
+                                              uint16_t *owner)
 {
     constexpr uint32_t kThreads = NW * 64;
     const uint32_t tid = threadIdx.x;
@@ -329,10 +366,15 @@ __device__ __forceinline__ uint32_t load_runs(const Bulk &A, uint32_t part, Runs
     uint32_t at = block_scan<NW>(sum, tmp, &total);
 #pragma unroll
     for (uint32_t j = 0; j < kMaxTiles / kThreads; ++j) {
-        if (j < per && t0 + j < A.tiles) {
-            R.first[t0 + j] = at;
-            R.shift[t0 + j] = (t0 + j) * A.tile + (s[j] & 0xFFFFu) - at;
-            at += (s[j] >> 16) - (s[j] & 0xFFFFu);
+        if (j < per) {
+            const uint32_t n = (s[j] >> 16) - (s[j] & 0xFFFFu);
+            if (t0 + j < A.tiles) {
+                R.first[t0 + j] = at;
+                R.shift[t0 + j] = (t0 + j) * A.tile + (s[j] & 0xFFFFu) - at;
+            }
+            if (total <= A.queue)
+                write_owner(owner, at, at + n, t0 + j);
+            at += n;
         }
     }
     if (tid == 0)
@@ -340,31 +382,21 @@ __device__ __forceinline__ uint32_t load_runs(const Bulk &A, uint32_t part, Runs
     return total;
 }
 
-// owner[q - q0] = the tile that operation q of the part comes from, for q0 <= q < q1: each
-// thread writes the runs of its tiles, a wavefront together the long ones.
+// owner[q - q0] = the tile that operation q of the part comes from, for q0 <= q < q1: a part that
+// is taken in pieces.
 template <int NW>
 __device__ __forceinline__ void own_runs(const Bulk &A, const Runs &R, uint32_t q0, uint32_t q1,
                                          uint16_t *owner)
 {
-    const uint32_t lane = lane_id();
     for (uint32_t t0 = threadIdx.x & ~63u; t0 < A.tiles; t0 += NW * 64) {
-        const uint32_t t = t0 + lane;
-        uint32_t lo = 0, hi = 0;
+        const uint32_t t = t0 + lane_id();
+        uint32_t lo = q0, hi = q0;
         if (t < A.tiles) {
             const uint32_t a = R.first[t], b = R.first[t + 1];
             lo = a < q0 ? q0 : a;
             hi = b < q1 ? b : q1;
         }
-        const bool is_long = hi > lo + 64u && hi > lo;
-        if (!is_long)
-            for (uint32_t q = lo; q < hi; ++q)
-                owner[q - q0] = (uint16_t)t;
-        for (uint64_t m = ballot(is_long); m; m &= m - 1) {
-            const uint32_t l = ffs0(m);
-            const uint32_t end = rl(hi, l);
-            for (uint32_t q = rl(lo, l) + lane; q < end; q += 64)
-                owner[q - q0] = (uint16_t)(t0 + l);
-        }
+        write_owner(owner, lo - q0, hi < lo ? lo - q0 : hi - q0, t);
     }
 }
 
@@ -398,15 +430,15 @@ template <bool KO> constexpr uint32_t kTagWords = KO ? 16u : 8u;
 // queue in LDS, not in registers: eight searches a thread in registers left three wavefronts per
 // SIMD where this form runs eight, and took 62 us where it takes 37: 2^22 searches, 2^22 keys.)
 // Lists longer than one slab are taken level by level: while many searches still run, the next
-// slab of every list that has one replaces its row; the last few are walked one per half
-// wavefront. A thread keeps the searches it has not answered as bits, search tid + i * threads
+// slab of every list that has one replaces its row; a wavefront with few left walks their lists
+// itself, one per half wavefront. A thread keeps the searches it has not answered as bits, search tid + i * threads
 // of the queue in bit i.
 template <bool KO, int NW>
 __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 {
     extern __shared__ uint64_t sm8[];
     constexpr uint32_t kThreads = NW * 64;
-    constexpr uint32_t kFew = NW * 8; // searches left to the half wavefronts: four each
+    constexpr uint32_t kFew = 8; // searches that a wavefront walks itself
     uint64_t *rows = sm8;
     // 16-byte aligned: an even number of 8-byte words comes before it
     uint32_t *tags = reinterpret_cast<uint32_t *>(rows + ((A.span * kRowWords + 1) & ~1u));
@@ -415,8 +447,7 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
     R.shift = R.first + A.tiles + 1;
     uint32_t *tmp = R.shift + A.tiles;
     uint32_t *sh = tmp + NW; // unanswered searches
-    uint32_t *list = sh + 1; // 2 kFew words: the last few searches' place and next slab
-    uint32_t *queue = list + 2 * kFew;
+    uint32_t *queue = sh + 1;
     uint16_t *owner = reinterpret_cast<uint16_t *>(queue + A.queue); // bit 15: found
     const uint32_t tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
     const uint32_t half = lane >> 5, slot = lane & 31;
@@ -456,13 +487,15 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
         }
     };
     fetch_rows(wv * 2); // in flight while the runs are read and summed
-    const uint32_t total = load_runs<NW>(A, part, R, tmp);
+    const uint32_t total = load_runs<NW>(A, part, R, tmp, owner);
     put_rows(wv * 2);
     bool fresh = true, have = true; // rows to be read; the first of them already there
     for (uint32_t q0 = 0; q0 < total; q0 += A.queue) {
         const uint32_t count = total - q0 < A.queue ? total - q0 : A.queue;
-        __syncthreads(); // the runs are there, and the last piece is done
-        own_runs<NW>(A, R, q0, q0 + count, owner);
+        if (total > A.queue) {
+            __syncthreads(); // the runs are there, and the last piece is done
+            own_runs<NW>(A, R, q0, q0 + count, owner);
+        }
         if (fresh) {
             for (uint32_t r0 = wv * 2 + (have ? NW * 2 * kRowLoads : 0); r0 < nb;
                  r0 += NW * 2 * kRowLoads) {
@@ -525,60 +558,68 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
                     undone |= bit;
                 }
             }
-            const uint32_t mine = (uint32_t)__popcll(undone);
+            uint32_t mine = (uint32_t)__popcll(undone);
             if (ballot(mine != 0)) {
-                const uint32_t s = wave_scan(mine);
-                if (lane == 63)
-                    atomicAdd(&sh[0], s);
+                uint32_t open = rl(wave_scan(mine), 63);
+                if (open <= kFew) {
+                    for (uint32_t i = 0; open; ++i) {
+                        const bool me = (undone >> i) & 1ull;
+                        const uint32_t q = tid + i * kThreads;
+                        const uint32_t key = me ? queue[q] : 0u;
+                        const uint32_t next =
+                            me ? (uint32_t)(rows[(bucket_fast(T, key) - b0) * kRowWords + 31] >> 32)
+                               : kEmpty;
+                        for (uint64_t m = ballot(me); m;) {
+                            const uint32_t ja = ffs0(m);
+                            m &= m - 1;
+                            const bool two = m != 0;
+                            const uint32_t jb = two ? ffs0(m) : ja;
+                            m = two ? m & (m - 1) : m;
+                            open -= two ? 2u : 1u;
+                            const uint32_t k = half ? rl(key, jb) : rl(key, ja);
+                            uint32_t nx = half ? (two ? rl(next, jb) : kEmpty) : rl(next, ja);
+                            uint32_t val = kEmpty, hit = 0, steps = 0;
+                            bool go = nx != kEmpty && pool_in_range(T, nx);
+                            while (ballot(go)) {
+                                const uint64_t x = go ? *gmem(pool_slab(T, nx) + slot) : 0ull;
+                                const bool is = go && slot < 31 &&
+                                                ((uint32_t)x == k ||
+                                                 (KO && (uint32_t)(x >> 32) == k));
+                                const uint32_t mm = (uint32_t)(ballot(is) >> (lane & 32u));
+                                const uint32_t src =
+                                    (lane & 32u) | (mm ? (uint32_t)__builtin_ctz(mm) : 31u);
+                                const uint32_t hv =
+                                    (uint32_t)__shfl((int)(uint32_t)(x >> 32), (int)src, 64);
+                                if (go && mm) {
+                                    val = KO ? k : hv;
+                                    hit = 1;
+                                    go = false;
+                                } else if (go) {
+                                    nx = hv;
+                                    go = nx != kEmpty && pool_in_range(T, nx) && ++steps <= limit;
+                                }
+                            }
+                            const uint32_t va = rl(val, 0), vb = rl(val, 32);
+                            const uint32_t ha = rl(hit, 0), hb = rl(hit, 32);
+                            if (lane == ja || (two && lane == jb)) {
+                                queue[q] = lane == ja ? va : vb;
+                                if (lane == ja ? ha : hb)
+                                    owner[q] |= 0x8000u;
+                            }
+                        }
+                    }
+                    undone = 0;
+                } else if (lane == 63) {
+                    atomicAdd(&sh[0], open);
+                }
             }
             __syncthreads();
-            const uint32_t left = sh[0];
-            if (left == 0)
+            if (sh[0] == 0)
                 break;
             __syncthreads();
             if (tid == 0)
                 sh[0] = 0;
             __syncthreads();
-            if (left <= kFew) {
-                for (uint64_t u = undone; u; u &= u - 1) {
-                    const uint32_t q = tid + ffs0(u) * kThreads;
-                    const uint32_t at = atomicAdd(&sh[0], 1u);
-                    list[at] = q;
-                    list[kFew + at] =
-                        (uint32_t)(rows[(bucket_fast(T, queue[q]) - b0) * kRowWords + 31] >> 32);
-                }
-                __syncthreads();
-                for (uint32_t e = wv * 2 + half; ballot(e < left); e += NW * 2) {
-                    const bool mine = e < left;
-                    const uint32_t q = mine ? list[e] : 0u, k = mine ? queue[q] : 0u;
-                    uint32_t nx = mine ? list[kFew + e] : kEmpty;
-                    uint32_t val = kEmpty, hit = 0, steps = 0;
-                    bool go = mine && pool_in_range(T, nx);
-                    while (ballot(go)) {
-                        const uint64_t x = go ? *gmem(pool_slab(T, nx) + slot) : 0ull;
-                        const bool is = go && slot < 31 &&
-                                        ((uint32_t)x == k || (KO && (uint32_t)(x >> 32) == k));
-                        const uint32_t mm = (uint32_t)(ballot(is) >> (lane & 32u));
-                        const uint32_t src = (lane & 32u) | (mm ? (uint32_t)__builtin_ctz(mm) : 31u);
-                        const uint32_t hv = (uint32_t)__shfl((int)(uint32_t)(x >> 32), (int)src, 64);
-                        if (go && mm) {
-                            val = KO ? k : hv;
-                            hit = 1;
-                            go = false;
-                        } else if (go) {
-                            nx = hv;
-                            go = nx != kEmpty && pool_in_range(T, nx) && ++steps <= limit;
-                        }
-                    }
-                    if (mine && slot == 0) {
-                        queue[q] = val;
-                        if (hit)
-                            owner[q] |= 0x8000u;
-                    }
-                }
-                __syncthreads();
-                break;
-            }
             // the next slab of every list replaces its row; the searches of a list without one
             // have all ended
             fresh = true;
@@ -686,13 +727,15 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
         }
     };
     fetch_rows(wv * 2); // in flight while the runs are read and summed
-    const uint32_t total = load_runs<NW>(A, part, R, tmp);
+    const uint32_t total = load_runs<NW>(A, part, R, tmp, owner);
     const uint32_t most = 4 * A.queue; // a part of repeated keys: the rest goes the plain way
     bool have = true;
     for (uint32_t q0 = 0; q0 < total; q0 += A.queue) {
         const uint32_t count = total - q0 < A.queue ? total - q0 : A.queue;
-        __syncthreads(); // the runs are there, and the last piece is done
-        own_runs<NW>(A, R, q0, q0 + count, owner);
+        if (total > A.queue) {
+            __syncthreads(); // the runs are there, and the last piece is done
+            own_runs<NW>(A, R, q0, q0 + count, owner);
+        }
         if (q0 >= most) {
             __syncthreads();
             for (uint32_t i = tid & ~63u; i < count; i += kThreads) {

@@ -2064,9 +2064,17 @@ struct BulkPlan {
 };
 
 constexpr size_t kLdsBytes = 160 * 1024;
-constexpr uint64_t kBulkSearches = 1u << 20, kBulkInserts = 1u << 19; // the smallest batches
-constexpr uint32_t kBulkBuckets = 1u << 12; // and tables
-constexpr uint32_t kBulkFill = 26; // slots taken per base slab after an insert call, at most
+// Where the bulk form begins, both forms measured on one box (us, plain / bulk):
+//   searches   2^21 at 38, 9.6 and 4.8 per bucket: 61 / 45, 78 / 54, 80 / 65; of popular keys
+//              (Zipf 1.1), which the plain form finds in the caches: 47 / 48, 56 / 59, 59 / 72;
+//              2^20: 33 / 28, and 27 / 33 of popular keys. So 2^21, and six per bucket.
+//   inserts    after a reset, at 19 and 6.4 per bucket: 2^18 57 / 37 and 35 / 35, 2^17 57 / 34
+//              and 28 / 24, 2^16 38 / 32 and 20 / 22, where four launches instead of one cost a
+//              program of small calls more on the host. So 2^17, and six per bucket.
+constexpr uint64_t kBulkSearches = 1u << 21, kBulkInserts = 1u << 17; // the smallest batches
+constexpr uint32_t kBulkPerBucket = 6;      // operations per bucket, at least
+constexpr uint32_t kBulkBuckets = 1u << 10; // a part has at least one, and parts fill the chip
+constexpr uint32_t kBulkFill = 26;          // slots taken per base slab after an insert call, at most
 
 // Whether the call takes the bulk form, and how. A part of about 2048 operations keeps a
 // workgroup of 8 wavefronts busy while three of them share a compute unit's LDS (2^22 searches of
@@ -2084,13 +2092,13 @@ bool bulk_plan(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
         return false;
     P->chunk = n < (1ull << 26) ? n : (1ull << 26);
     const uint64_t m = P->chunk;
-    if (m < (ins ? kBulkInserts : kBulkSearches) || m / 4 < B || B < kBulkBuckets)
+    if (m < (ins ? kBulkInserts : kBulkSearches) || m / kBulkPerBucket < B || B < kBulkBuckets)
         return false;
     // inserts that the base slabs have no room for are made the plain way, after the others:
     // nothing is gained where they are many
     if (ins && __atomic_load_n(&t->taken, __ATOMIC_RELAXED) + n > (uint64_t)B * kBulkFill)
         return false;
-    P->rows = m <= (3u << 19) ? 4 : m <= (1u << 23) ? 16 : 32;
+    P->rows = m <= (3u << 19) ? 4 : m <= (3u << 20) ? 8 : m <= (1u << 23) ? 16 : 32;
     Bulk &A = P->a;
     A.tile = P->rows * kSplitThreads;
     A.tiles = (uint32_t)((m + A.tile - 1) / A.tile);
@@ -2120,12 +2128,14 @@ bool bulk_plan(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
     A.queue = (uint32_t)(avg + 6 * sqrt(avg) + 64) & ~3u;
     if (A.queue > 32 * P->waves * 64)
         A.queue = 32 * P->waves * 64;
-    A.hot = ins ? 0xFFFFu : 3 * (A.tile / A.parts) + 16;
+    // more of one part in a tile than distinct keys make by chance
+    const double run = (double)A.tile / A.parts;
+    A.hot = ins ? 0xFFFFu : (uint32_t)(run + 5 * sqrt(run)) + 4;
     P->split_lds = ((size_t)A.tile + A.row + kSplitThreads / 64 + 1) * 4;
     const size_t runs = 8 * (size_t)A.tiles + 4 + 4 * P->waves;
     P->part_lds = ins ? (size_t)span * kInsRowBytes + 8 + runs + 4 * (size_t)A.queue
                       : (size_t)span * (kRowWords * 8 + (ko ? 64 : 32)) + 8 + runs + 4 +
-                            64 * P->waves + 6 * (size_t)A.queue;
+                            6 * (size_t)A.queue;
     P->merge_lds = (size_t)A.tile * (ins ? 1 : 5);
     if (P->split_lds > kLdsBytes || P->part_lds > kLdsBytes || P->merge_lds > kLdsBytes)
         return false;
@@ -2159,8 +2169,10 @@ bool allow_lds(F fn, size_t bytes)
 template <bool Vals>
 auto split_fn(uint32_t rows)
 {
-    return rows == 32 ? split_kernel<32, Vals> : rows == 16 ? split_kernel<16, Vals>
-                                                            : split_kernel<4, Vals>;
+    return rows == 32   ? split_kernel<32, Vals>
+           : rows == 16 ? split_kernel<16, Vals>
+           : rows == 8  ? split_kernel<8, Vals>
+                        : split_kernel<4, Vals>;
 }
 
 // The bulk form of one search (vals null) or insert call.
@@ -2179,6 +2191,7 @@ sh_status_t launch_bulk(sh_table *t, const BulkPlan &P, const uint32_t *keys, co
     const auto split = ins ? split_fn<true>(P.rows) : split_fn<false>(P.rows);
     const auto merge = P.rows == 32   ? merge_kernel<32>
                        : P.rows == 16 ? merge_kernel<16>
+                       : P.rows == 8  ? merge_kernel<8>
                                       : merge_kernel<4>;
     const bool wide = P.waves == 16;
     const auto part = ins  ? (wide ? insert_kernel<16> : insert_kernel<8>)

@@ -169,8 +169,8 @@ def _stream(stream) -> int:
 # sh_capture_begin calls of this thread that sh_capture_end has not ended
 _capturing = threading.local()
 
-#: No batch below this takes the bulk form (the library's own lines lie at or above it).
-_BULK_MIN = 1 << 19
+#: No batch below these takes the bulk form (the library's own lines lie at or above them).
+_BULK_MIN = {SH_OP_SEARCH: 1 << 21, SH_OP_INSERT: 1 << 17}
 
 
 def sh_bulk_bytes(t, kind: int, n: int, stream=None) -> int:
@@ -183,7 +183,7 @@ def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     been enqueued. A stream that torch does not own, a capture in progress and a device without
     room take the plain form."""
     n = keys.numel()
-    if n < _BULK_MIN or getattr(_capturing, "depth", 0):
+    if n < _BULK_MIN[kind] or getattr(_capturing, "depth", 0):
         return None
     cur = torch.cuda.current_stream()
     if stream is None or _stream(stream) == cur.cuda_stream:

@@ -15,7 +15,7 @@ from test_gpu_parity import assert_same_table
 
 pytestmark = pytest.mark.gpu
 M = S.SH_SLAB_PAIRS
-SMALLEST = {S.SH_OP_SEARCH: 1 << 20, S.SH_OP_INSERT: 1 << 19}
+SMALLEST = {S.SH_OP_SEARCH: 1 << 21, S.SH_OP_INSERT: 1 << 17}
 
 
 def say(*a):
@@ -76,16 +76,16 @@ def table(seed, n, B, **mode):
     return S.SlabHash(B, S.pool_slabs_bound(2 * n), a, b, **mode), a, b
 
 
-# batch sizes at the smallest batch, around a whole tile of 4096 and of 16384, and at the line
-# where the tile grows (3 * 2^19); buckets from one part's worth up to the line n / 4
-@pytest.mark.parametrize("n,B", [(1 << 20, 54343), ((1 << 20) + 1, 54343), ((1 << 20) + 4095, 4096),
-                                 (3 << 19, 100003), ((3 << 19) + 1, 100003),
-                                 (2097152 + 16383, 500000), (1300003, 300007)])
+# the smallest batch; around a whole tile of 8192 and of 16384 and the line where the tile grows
+# (3 * 2^20); buckets from one per part up to the line of six operations each
+@pytest.mark.parametrize("n,B", [(1 << 21, 54343), ((1 << 21) + 1, 1024), ((1 << 21) + 8191, 4096),
+                                 (3 << 20, 100003), ((3 << 20) + 1, 100003),
+                                 ((3 << 20) + 16383, 500000), (2300003, 300007)])
 @pytest.mark.parametrize("mode", ["pairs", "duplicates", "keys_only", "both"])
 def test_search(n, B, mode):
     say("case: bulk search", n, B, mode)
     kw = dict(duplicates=mode in ("duplicates", "both"), keys_only=mode in ("keys_only", "both"))
-    t, _, _ = table(31 + B, 1 << 20, B, **kw)
+    t, _, _ = table(31 + B, 1 << 21, B, **kw)
     keys = torch.from_numpy(W.distinct_keys(5, 0, n).view(np.int32)).cuda()
     held = keys[:n // 2]
     vals = held ^ 0x1234567
@@ -109,9 +109,9 @@ def test_search(n, B, mode):
 
 
 def test_search_long_lists_and_popular_keys():
-    """Lists of about nine slabs; batches of one key, of few keys and of Zipf ranks."""
+    """Lists of about eight slabs; batches of one key, of few keys and of Zipf ranks."""
     say("case: bulk search, long lists and popular keys")
-    n, B = 1 << 20, 4096
+    n, B = 1 << 21, 8192
     t, _, _ = table(77, n, B)
     keys = torch.from_numpy(W.distinct_keys(9, 0, n).view(np.int32)).cuda()
     t.insert(keys, ~keys)
@@ -125,10 +125,10 @@ def test_search_long_lists_and_popular_keys():
         assert same(bulk_search(t, q), plain_search(t, q)), i
 
 
-# the smallest batch and the fewest inserts per bucket, a full base slab's worth, and both sides
-# of the line where the tile grows; tables with room for a second batch and without
-@pytest.mark.parametrize("n,B", [(1 << 19, 20200), ((1 << 19) + 1, 131072), (700001, 60013),
-                                 (3 << 19, 78643), ((3 << 19) + 5, 150001), (1 << 20, 43691)])
+# the smallest batch, the fewest inserts per bucket and a full base slab's worth of them, and both
+# sides of the line where the tile grows; tables with room for a second batch and without
+@pytest.mark.parametrize("n,B", [(1 << 17, 5043), ((1 << 17) + 1, 21845), (700001, 60013),
+                                 (3 << 19, 78643), ((3 << 19) + 5, 150001), (1 << 19, 20200)])
 def test_insert(oracle_mod, n, B):
     """Fresh keys, the same keys with new values, and a batch with repeated, present, fresh and
     reserved keys: statuses, values and the whole structure against the oracle."""
@@ -259,27 +259,27 @@ def test_two_bulk_inserts_and_plain_inserts_at_once():
 def test_where_the_plain_form_serves():
     """Calls that keep the plain form, and arguments that are refused."""
     say("case: bulk form's lines")
-    t, _, _ = table(3, 1 << 20, 50000)
+    t, _, _ = table(3, 1 << 21, 20000)
     for kind, least in SMALLEST.items():
         assert S.sh_bulk_bytes(t.handle, kind, least) > 0
         assert S.sh_bulk_bytes(t.handle, kind, least - 1) == 0
         assert S.sh_bulk_bytes(t.handle, kind, 0) == 0
     for kind in (S.SH_OP_DELETE, S.SH_KIND_MIXED, 17):
         assert S.sh_bulk_bytes(t.handle, kind, 1 << 21) == 0
-    wide, _, _ = table(3, 1 << 10, (1 << 18) + 1)
-    assert S.sh_bulk_bytes(wide.handle, S.SH_OP_SEARCH, 1 << 20) == 0  # fewer than 4 per bucket
-    few, _, _ = table(3, 1 << 20, 4095)
-    assert S.sh_bulk_bytes(few.handle, S.SH_OP_SEARCH, 1 << 20) == 0
-    assert S.sh_bulk_bytes(t.handle, S.SH_OP_INSERT, 26 * 50000 + 1) == 0
-    flagged, _, _ = table(3, 1 << 10, 50000, keys_only=True)
+    wide, _, _ = table(3, 1 << 10, (1 << 21) // 6 + 1)  # fewer than six per bucket
+    assert S.sh_bulk_bytes(wide.handle, S.SH_OP_SEARCH, 1 << 21) == 0
+    few, _, _ = table(3, 1 << 20, 1023)
+    assert S.sh_bulk_bytes(few.handle, S.SH_OP_SEARCH, 1 << 21) == 0
+    assert S.sh_bulk_bytes(t.handle, S.SH_OP_INSERT, 26 * 20000 + 1) == 0
+    flagged, _, _ = table(3, 1 << 10, 20000, keys_only=True)
     assert S.sh_bulk_bytes(flagged.handle, S.SH_OP_INSERT, 1 << 20) == 0
-    assert S.sh_bulk_bytes(flagged.handle, S.SH_OP_SEARCH, 1 << 20) > 0
+    assert S.sh_bulk_bytes(flagged.handle, S.SH_OP_SEARCH, 1 << 21) > 0
     t.set_launch(16, 32)
-    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 1 << 20) == 0
+    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 1 << 21) == 0
     t.set_launch(0, 0, S.SH_LAUNCH_COUNTERS)
-    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 1 << 20) == 0
+    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 1 << 21) == 0
     t.set_launch()
-    n = 1 << 20
+    n = 1 << 21
     k = torch.from_numpy(W.distinct_keys(41, 0, n).view(np.int32)).cuda()
     t.insert(k, ~k)
     v = torch.empty(n, dtype=torch.int32, device="cuda")
