@@ -158,9 +158,21 @@ def _check(fn: str, code: int) -> None:
         raise SlabHashError(fn, code)
 
 
+# The current device's current stream as a number: torch.cuda.current_stream() builds a Stream
+# object each time (2.7 us of a small call's 11 us; this, 0.15 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _current_stream() -> int:
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -185,9 +197,8 @@ def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     n = keys.numel()
     if n < _BULK_MIN[kind] or getattr(_capturing, "depth", 0):
         return None
-    cur = torch.cuda.current_stream()
-    if stream is None or _stream(stream) == cur.cuda_stream:
-        stream = cur
+    if stream is None or _stream(stream) == _current_stream():
+        stream = torch.cuda.current_stream()
     elif type(stream) is not torch.cuda.Stream:
         return None
     nbytes = sh_bulk_bytes(t, kind, n, stream)
