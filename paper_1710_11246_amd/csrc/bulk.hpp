@@ -20,22 +20,6 @@ constexpr uint32_t kMaxSpan = 1000;       // buckets of a part (insert_kernel's 
 constexpr uint32_t kRowWords = 33;        // a slab's row in LDS: 32 words and one of padding, so
                                           // that one slot of many rows spreads over the banks
 
-// x / d for 32-bit x: m = magic_for(d) gives a quotient at most one too small.
-__host__ __device__ inline uint32_t magic_for(uint32_t d)
-{
-    return d <= 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / d);
-}
-__device__ __forceinline__ uint32_t div_magic(uint32_t x, uint32_t d, uint32_t m, uint32_t *rem)
-{
-    uint32_t q = __umulhi(x, m), r = x - q * d;
-    if (r >= d) {
-        r -= d;
-        ++q;
-    }
-    *rem = r;
-    return q;
-}
-
 struct Bulk {
     uint32_t span, span_magic;   // buckets per part
     uint32_t parts, tiles, tile; // tile: operations per tile
@@ -50,17 +34,6 @@ struct Bulk {
     uint16_t *place;             // place of each operation of the batch in its tile
     uint8_t *flag;               // per operation, in tile order
 };
-
-__device__ __forceinline__ uint32_t bucket_fast(const View &T, uint32_t k)
-{
-    uint64_t x = (uint64_t)T.a * k + T.b;
-    uint64_t t = (x >> 32) * 5u + (x & 0xFFFFFFFFull);
-    t = (t >> 32) * 5u + (t & 0xFFFFFFFFull);
-    const uint32_t r = (t >= kPrime) ? (uint32_t)(t - kPrime) : (uint32_t)t;
-    uint32_t rem;
-    div_magic(r, T.B, T.bmagic, &rem);
-    return rem;
-}
 
 // Inclusive sum over the wavefront's lanes: four shifts within rows of 16 lanes, then the sums of
 // the rows before (lane 15 of rows 0 and 2 to rows 1 and 3, lane 31 to rows 2 and 3).
@@ -157,7 +130,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_kernel(View T, Bulk A,
     for (int j = 0; j < R; ++j) {
         if (index(j) < count) {
             uint32_t rem;
-            const uint32_t p = div_magic(bucket_fast(T, k[j]), A.span, A.span_magic, &rem);
+            const uint32_t p = div_magic(bucket_of(T, k[j]), A.span, A.span_magic, &rem);
             pr[j] = (p << 16) | rank_of(p);
             bad = bad || k[j] >= reserve_from;
         }
@@ -528,7 +501,7 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
                 if (level && !(undone & bit))
                     continue;
                 const uint32_t key = queue[q];
-                const uint32_t r = bucket_fast(T, key) - b0;
+                const uint32_t r = bucket_of(T, key) - b0;
                 const uint64_t *row = rows + r * kRowWords;
                 const uint32_t pattern = tag_of(key) * 0x01010101u;
                 // reserved keys match nothing
@@ -567,7 +540,7 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
                         const uint32_t q = tid + i * kThreads;
                         const uint32_t key = me ? queue[q] : 0u;
                         const uint32_t next =
-                            me ? (uint32_t)(rows[(bucket_fast(T, key) - b0) * kRowWords + 31] >> 32)
+                            me ? (uint32_t)(rows[(bucket_of(T, key) - b0) * kRowWords + 31] >> 32)
                                : kEmpty;
                         for (uint64_t m = ballot(me); m;) {
                             const uint32_t ja = ffs0(m);
@@ -763,7 +736,7 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                     continue;
                 uint32_t l = kNoLine;
                 if (k[u] != kEmpty) {
-                    const uint32_t r = bucket_fast(T, k[u]) - b0;
+                    const uint32_t r = bucket_of(T, k[u]) - b0;
                     const uint32_t at = atomicAdd(&cnt[r], 1u);
                     l = kNoLine | kLater;
                     if (at < 32u) {
@@ -941,7 +914,7 @@ __global__ __launch_bounds__(kBlock) void later_kernel(View T, Bulk A, uint32_t 
         c.key = in ? A.key[pos] : kEmpty;
         c.val = in ? A.val[pos] : 0u;
         c.op = kInsert;
-        run_chunk<kInsert, false, false, NQ>(T, al, cnt, lds[wl_], c, nullptr, A.flag, pos, count,
+        run_chunk<kInsert, false, false, NQ, true>(T, al, cnt, lds[wl_], c, nullptr, A.flag, pos, count,
                                              0u);
     }
 }

@@ -151,16 +151,35 @@ __device__ __forceinline__ uint32_t wl(uint32_t x, uint32_t j, uint32_t v)
 // (gfx9 encoding: vmcnt 0, expcnt 7, lgkmcnt 15 left unconstrained).
 __device__ __forceinline__ void wait_vm_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// x / d and x % d for 32-bit x, by a multiplication: m = magic_for(d) gives a quotient that is at
+// most one too small.
+__host__ __device__ inline uint32_t magic_for(uint32_t d)
+{
+    return d <= 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / d);
+}
+__device__ __forceinline__ uint32_t div_magic(uint32_t x, uint32_t d, uint32_t m, uint32_t *rem)
+{
+    uint32_t q = __umulhi(x, m), r = x - q * d;
+    if (r >= d) {
+        r -= d;
+        ++q;
+    }
+    *rem = r;
+    return q;
+}
+
 // Universal hash of the "Slab Hash" subsection: ((a k + b) mod p) mod B with p = 2^32 - 5.
 // a k + b < 2^64; since 2^32 = 5 (mod p) two folds of the high half bring it below 2^32 + 30,
 // and one conditional subtraction finishes the reduction mod p.
-__device__ __forceinline__ uint32_t bucket_of(uint32_t k, uint32_t a, uint32_t b, uint32_t B)
+__device__ __forceinline__ uint32_t bucket_of(const View &T, uint32_t k)
 {
-    uint64_t x = (uint64_t)a * k + b;
+    uint64_t x = (uint64_t)T.a * k + T.b;
     uint64_t t = (x >> 32) * 5u + (x & 0xFFFFFFFFull);
     t = (t >> 32) * 5u + (t & 0xFFFFFFFFull);
-    uint32_t r = (t >= kPrime) ? (uint32_t)(t - kPrime) : (uint32_t)t;
-    return r % B;
+    const uint32_t r = (t >= kPrime) ? (uint32_t)(t - kPrime) : (uint32_t)t;
+    uint32_t rem;
+    div_magic(r, T.B, T.bmagic, &rem);
+    return rem;
 }
 
 // Every table access goes through a global-address-space pointer: slab and bitmap addresses
@@ -593,7 +612,7 @@ __device__ __forceinline__ ChunkIn load_chunk(const uint8_t *__restrict__ ops,
 // (lanes 32..63); bits of `todo` name the ops still running (pairs with neither are skipped);
 // L.key holds each op's key and `op` this lane's op kind. Returns this lane's outcome: (code << 8
 // | slot) in the high word, the payload in the low word.
-template <int K, bool Dup, int NQ>
+template <int K, bool Dup, int NQ, bool Locks>
 __device__ __forceinline__ uint64_t decide_kv(const uint64_t (&pre)[NQ], uint64_t todo,
                                               const WaveLds &L, uint32_t op)
 {
@@ -612,9 +631,9 @@ __device__ __forceinline__ uint64_t decide_kv(const uint64_t (&pre)[NQ], uint64_
         kmv = wl(kmv, 2 * q + 1, (uint32_t)(km >> 32));
         if constexpr (kHasIns) {
             // a locked slot counts as the empty slot that it was: the swap then meets the lock
-            const uint64_t em = ballot(Dup ? w == kEmptyPair
-                                           : (uint32_t)w == kEmpty &&
-                                                 (uint32_t)(w >> 32) >= (uint32_t)(kLockPair >> 32));
+            const uint64_t em = ballot(Locks ? (uint32_t)w == kEmpty &&
+                                                   (uint32_t)(w >> 32) >= (uint32_t)(kLockPair >> 32)
+                                             : w == kEmptyPair);
             emv = wl(emv, 2 * q, (uint32_t)em);
             emv = wl(emv, 2 * q + 1, (uint32_t)(em >> 32));
         }
@@ -660,7 +679,10 @@ __device__ __forceinline__ uint64_t decide_kv(const uint64_t (&pre)[NQ], uint64_
 // One chunk of up to 2 NQ ops (lane l < count holds op i, with inputs `c`) on table T,
 // processed in rounds until every op has finished (see the description above). NQ is the
 // number of op pairs, and so the length of each round's straight run of loads.
-template <int K, bool Dup, bool KO, int NQ = 32>
+//
+// Locks: a bulk insert may hold slabs of the table meanwhile (unique-key pair tables that no
+// multi-table object owns; looking for its mark made a batched launch 0.7% slower).
+template <int K, bool Dup, bool KO, int NQ, bool Locks>
 __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, ChunkIn c,
                           uint32_t *__restrict__ vout, uint8_t *__restrict__ sout, uint64_t i,
                           uint32_t count, uint32_t flags)
@@ -682,7 +704,7 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
     if (res_m)
         raise_error(T, SH_ERR_RESERVED_KEY, lane, ffs0(res_m));
     const bool act = in && !reserved && op <= 2;
-    const uint32_t bkt = act ? bucket_of(key, T.a, T.b, T.B) : 0u;
+    const uint32_t bkt = act ? bucket_of(T, key) : 0u;
     L.key[lane] = key;
     if constexpr (K == kMixed && KO)
         L.op[lane] = op;
@@ -721,7 +743,7 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
         // ---- 2. decide ----
         uint64_t outcome = 0;
         if constexpr (!KO) {
-            outcome = decide_kv<K, Dup, NQ>(pre, todo, L, op);
+            outcome = decide_kv<K, Dup, NQ, Locks>(pre, todo, L, op);
         } else {
             // Key-only slabs (two entries per lane, entries 2 slot in lo and 2 slot + 1 in hi):
             // the target lane of each op writes the op's outcome to the op's LDS cell.
@@ -913,7 +935,7 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                     // return; at most the 31 slots of this slab. (With duplicates, empty slots
                     // need not be a suffix, so a lost insert re-reads its slab next round.)
                     for (;;) {
-                        if (old == kLockPair) {
+                        if (Locks && old == kLockPair) {
                             lost = true; // a bulk insert holds the slab: read it again
                             break;
                         }
@@ -1090,7 +1112,7 @@ __global__ __launch_bounds__(kBlock) void ops_kernel(View T, const uint8_t *__re
         const uint64_t base = c * C;
         const uint32_t count = (uint32_t)((n - base < C) ? n - base : C);
         const ChunkIn cur = load_chunk<K, KO>(ops, keys, vals, base, count);
-        run_chunk<K, Dup, KO, NQ>(T, al, cnt, lds[wl_], cur, vout, sout, base + lane_id(),
+        run_chunk<K, Dup, KO, NQ, !Dup && !KO>(T, al, cnt, lds[wl_], cur, vout, sout, base + lane_id(),
                                   count, flags);
     }
     if (flags & kFlagCounters)
@@ -1186,7 +1208,7 @@ __global__ __launch_bounds__(kBlock) void multi_kernel(const View *__restrict__ 
             if (count > n_ops - base)
                 count = n_ops - base;
         }
-        run_chunk<kMixed, false, false, NQ>(
+        run_chunk<kMixed, false, false, NQ, false>(
             Tv, al, cnt, lds[wl_],
             load_chunk<kMixed, false>(ops, keys, vals, base, (uint32_t)count), vout, sout,
             base + lane_id(), (uint32_t)count, flags);
@@ -1491,7 +1513,7 @@ __global__ __launch_bounds__(kBlock) void all_kernel(View T, const uint32_t *__r
             raise_error(T, SH_ERR_RESERVED_KEY, lane, ffs0(res_m));
         kk[lane] = key;
         uu[lane] = (in && key != kEmpty && !(KO && key == kTombKey))
-                       ? bucket_of(key, T.a, T.b, T.B)
+                       ? bucket_of(T, key)
                        : 0u;
         // each op's output range, read once per chunk by the op's own lane (the pairs below
         // take theirs from that lane)
@@ -2072,6 +2094,8 @@ constexpr size_t kLdsBytes = 160 * 1024;
 //              and 28 / 24, 2^16 38 / 32 and 20 / 22, where four launches instead of one cost a
 //              program of small calls more on the host. So 2^17, and six per bucket.
 constexpr uint64_t kBulkSearches = 1u << 21, kBulkInserts = 1u << 17; // the smallest batches
+constexpr uint32_t kBulkCached = 1u << 15;  // base slabs that the L2s hold: 2^21 searches of them
+constexpr uint64_t kBulkCachedSearches = 3u << 20; // take 42 / 46, 2^22 85 / 65
 constexpr uint32_t kBulkPerBucket = 6;      // operations per bucket, at least
 constexpr uint32_t kBulkBuckets = 1u << 10; // a part has at least one, and parts fill the chip
 constexpr uint32_t kBulkFill = 26;          // slots taken per base slab after an insert call, at most
@@ -2087,12 +2111,12 @@ bool bulk_plan(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
     const bool ins = kind == kInsert;
     const uint32_t B = t->v.B;
     const bool ko = (t->v.mode & SH_TABLE_KEYS_ONLY) != 0;
-    if ((kind != kSearch && kind != kInsert) || (ins && t->v.mode) || t->flags ||
+    if ((kind != kSearch && kind != kInsert) || (ins && (t->v.mode || t->embedded)) || t->flags ||
         t->waves_per_cu || t->ops_per_wave)
         return false;
     P->chunk = n < (1ull << 26) ? n : (1ull << 26);
     const uint64_t m = P->chunk;
-    if (m < (ins ? kBulkInserts : kBulkSearches) || m / kBulkPerBucket < B || B < kBulkBuckets)
+    if (m < (ins ? kBulkInserts : B < kBulkCached ? kBulkCachedSearches : kBulkSearches) || m / kBulkPerBucket < B || B < kBulkBuckets)
         return false;
     // inserts that the base slabs have no room for are made the plain way, after the others:
     // nothing is gained where they are many

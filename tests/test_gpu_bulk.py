@@ -15,7 +15,7 @@ from test_gpu_parity import assert_same_table
 
 pytestmark = pytest.mark.gpu
 M = S.SH_SLAB_PAIRS
-SMALLEST = {S.SH_OP_SEARCH: 1 << 21, S.SH_OP_INSERT: 1 << 17}
+SMALLEST = {S.SH_OP_SEARCH: 3 << 20, S.SH_OP_INSERT: 1 << 17}
 
 
 def say(*a):
@@ -78,7 +78,7 @@ def table(seed, n, B, **mode):
 
 # the smallest batch; around a whole tile of 8192 and of 16384 and the line where the tile grows
 # (3 * 2^20); buckets from one per part up to the line of six operations each
-@pytest.mark.parametrize("n,B", [(1 << 21, 54343), ((1 << 21) + 1, 1024), ((1 << 21) + 8191, 4096),
+@pytest.mark.parametrize("n,B", [(1 << 21, 54343), ((3 << 20) + 1, 1024), ((3 << 20) + 8191, 4096),
                                  (3 << 20, 100003), ((3 << 20) + 1, 100003),
                                  ((3 << 20) + 16383, 500000), (2300003, 300007)])
 @pytest.mark.parametrize("mode", ["pairs", "duplicates", "keys_only", "both"])
@@ -111,7 +111,7 @@ def test_search(n, B, mode):
 def test_search_long_lists_and_popular_keys():
     """Lists of about eight slabs; batches of one key, of few keys and of Zipf ranks."""
     say("case: bulk search, long lists and popular keys")
-    n, B = 1 << 21, 8192
+    n, B = 3 << 20, 12288
     t, _, _ = table(77, n, B)
     keys = torch.from_numpy(W.distinct_keys(9, 0, n).view(np.int32)).cuda()
     t.insert(keys, ~keys)
@@ -266,20 +266,23 @@ def test_where_the_plain_form_serves():
         assert S.sh_bulk_bytes(t.handle, kind, 0) == 0
     for kind in (S.SH_OP_DELETE, S.SH_KIND_MIXED, 17):
         assert S.sh_bulk_bytes(t.handle, kind, 1 << 21) == 0
+    big, _, _ = table(3, 1 << 10, 1 << 15)  # more than the caches hold
+    assert S.sh_bulk_bytes(big.handle, S.SH_OP_SEARCH, 1 << 21) > 0
+    assert S.sh_bulk_bytes(big.handle, S.SH_OP_SEARCH, (1 << 21) - 1) == 0
     wide, _, _ = table(3, 1 << 10, (1 << 21) // 6 + 1)  # fewer than six per bucket
     assert S.sh_bulk_bytes(wide.handle, S.SH_OP_SEARCH, 1 << 21) == 0
     few, _, _ = table(3, 1 << 20, 1023)
-    assert S.sh_bulk_bytes(few.handle, S.SH_OP_SEARCH, 1 << 21) == 0
+    assert S.sh_bulk_bytes(few.handle, S.SH_OP_SEARCH, 3 << 20) == 0
     assert S.sh_bulk_bytes(t.handle, S.SH_OP_INSERT, 26 * 20000 + 1) == 0
     flagged, _, _ = table(3, 1 << 10, 20000, keys_only=True)
     assert S.sh_bulk_bytes(flagged.handle, S.SH_OP_INSERT, 1 << 20) == 0
-    assert S.sh_bulk_bytes(flagged.handle, S.SH_OP_SEARCH, 1 << 21) > 0
+    assert S.sh_bulk_bytes(flagged.handle, S.SH_OP_SEARCH, 3 << 20) > 0
     t.set_launch(16, 32)
-    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 1 << 21) == 0
+    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 3 << 20) == 0
     t.set_launch(0, 0, S.SH_LAUNCH_COUNTERS)
-    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 1 << 21) == 0
+    assert S.sh_bulk_bytes(t.handle, S.SH_OP_SEARCH, 3 << 20) == 0
     t.set_launch()
-    n = 1 << 21
+    n = 3 << 20
     k = torch.from_numpy(W.distinct_keys(41, 0, n).view(np.int32)).cuda()
     t.insert(k, ~k)
     v = torch.empty(n, dtype=torch.int32, device="cuda")
