@@ -326,6 +326,7 @@ struct Alloc {
     uint32_t total_moves;
     uint32_t start; // first block tried (taken modulo the blocks in use)
     uint32_t rot;   // this wavefront's rotation of the lane priority order
+    uint32_t brot;  // and of the bits within a word
     uint32_t lost;  // claims that found their bit already taken by another wavefront
     bool full;      // this wavefront found the pool exhausted
 };
@@ -384,6 +385,15 @@ __device__ __forceinline__ void alloc_preload(const View &T, Alloc &s, uint32_t 
     alloc_goto(T, s, first + s.start % (s.nact - first), lane);
 }
 
+// The free slab of a bitmap word that this wavefront tries: the first from bit `brot` up, around.
+// Wavefronts that hold copies of one word would otherwise all claim its lowest free bit, and each
+// but one would try again (2^18 inserts that add 5733 slabs to lists: 21,500 lost claims, 75 us).
+__device__ __forceinline__ uint32_t pick_bit(uint32_t free_bits, uint32_t brot)
+{
+    const uint32_t r = __builtin_rotateright32(free_bits, brot);
+    return ((uint32_t)__builtin_ctz(r) + brot) & 31u;
+}
+
 __device__ uint32_t wave_alloc(const View &T, Alloc &s, uint32_t lane)
 {
     if (T.total_blocks == 0 || s.full)
@@ -403,7 +413,7 @@ __device__ uint32_t wave_alloc(const View &T, Alloc &s, uint32_t lane)
             const uint32_t l = (ffs0(r) + s.rot) & 63u;
             uint32_t got = kEmpty;
             if (lane == l) {
-                const uint32_t bit = (uint32_t)__builtin_ctz(~s.word);
+                const uint32_t bit = pick_bit(~s.word, s.brot);
                 const uint32_t m = 1u << bit;
                 const uint32_t old = or32(&s.row[l], m);
                 s.word = old | m;
@@ -504,24 +514,16 @@ __device__ uint32_t wave_alloc_many(const View &T, Alloc &s, uint32_t lane, uint
     return got;
 }
 
-// The bits this lane claims so that the wavefront's lanes together claim `need` free slabs of
-// the resident block (in the rotated lane order of wave_alloc_many, lowest free bits first); 0
-// for every lane when there is no resident block yet. Fewer than `need` when the block holds
-// fewer free slabs.
-__device__ __forceinline__ uint32_t claim_plan(const Alloc &s, uint32_t lane, uint32_t need)
+// The bit this lane claims of its word so that the wavefront claims one free slab of the resident
+// block, in wave_alloc's order; 0 for every other lane, and for all when there is no resident
+// block yet or it is full.
+__device__ __forceinline__ uint32_t claim_plan(const Alloc &s, uint32_t lane)
 {
-    if (s.blk == kEmpty || s.full)
+    const uint64_t free_lanes = s.blk == kEmpty || s.full ? 0ull : ballot(s.word != kEmpty);
+    if (!free_lanes)
         return 0u;
-    const uint32_t fw = ~s.word;
-    uint32_t total;
-    const uint32_t before = rotated_scan((uint32_t)__popc(fw), lane, s.rot, &total);
-    uint32_t take = before >= need ? 0u : need - before;
-    uint32_t m = 0, f = fw;
-    for (; take && f; --take) {
-        m |= f & (0u - f);
-        f &= f - 1u;
-    }
-    return m;
+    const uint64_t r = (free_lanes >> s.rot) | (free_lanes << ((64u - s.rot) & 63u));
+    return lane == ((ffs0(r) + s.rot) & 63u) ? 1u << pick_bit(~s.word, s.brot) : 0u;
 }
 
 __device__ __forceinline__ void slab_free(const View &T, uint32_t idx)
@@ -577,7 +579,6 @@ struct WaveLds {
     uint64_t msg[64];
     uint32_t key[64];
     uint32_t op[64];
-    uint32_t claimed[64]; // slabs the round's bitmap claims won, in rotated lane order
 };
 
 // The inputs of one chunk, one op per lane (lanes past the chunk's end hold no op).
@@ -845,7 +846,7 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
             alloc_m = ballot(code == kMsgGrow);
             alloc_m &= 0ull - alloc_m;
             if (alloc_m) {
-                claim_m = claim_plan(al, lane, 1u);
+                claim_m = claim_plan(al, lane);
                 if (claim_m)
                     claim_old = or32(&al.row[lane], claim_m);
             }
@@ -978,17 +979,15 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                 if (claim_m)
                     al.word = claim_old | claim_m;
                 al.lost += (uint32_t)__popcll(ballot((claim_m & claim_old) != 0u));
-                uint32_t served;
-                uint32_t at = rotated_scan((uint32_t)__popc(got_m), lane, al.rot, &served);
-                uint32_t *claimed = L.claimed;
-                for (uint32_t w = got_m; w; w &= w - 1u)
-                    claimed[at++] = al.code + lane * 32 + (uint32_t)__builtin_ctz(w);
-                if (served)
+                const uint64_t got = ballot(got_m != 0u);
+                if (got)
                     al.moves = 0;
-                __builtin_amdgcn_wave_barrier();
                 const bool grows = (alloc_m >> lane) & 1;
-                const uint32_t g = (uint32_t)__popcll(alloc_m & ((1ull << lane) - 1ull));
-                uint32_t idx = (grows && g < served) ? claimed[g] : kEmpty;
+                const uint32_t slab =
+                    got ? rl(al.code + lane * 32 + (uint32_t)__builtin_ctz(got_m | 0x80000000u),
+                             ffs0(got))
+                        : kEmpty;
+                uint32_t idx = grows ? slab : kEmpty;
                 // if the claim could not serve it (the resident block's free bits were taken):
                 // the allocator proper, moving on through the blocks
                 uint64_t rest = alloc_m & ~ballot(idx != kEmpty);
@@ -1087,6 +1086,7 @@ __device__ __forceinline__ void alloc_init(Alloc &al, uint32_t wave, uint32_t se
     al.full = false;
     al.start = mix32(wave * 0x9E3779B9u + seq);
     al.rot = mix32(al.start) & 63u;
+    al.brot = mix32(al.start) >> 27;
 }
 
 template <int K, bool Dup, bool KO, int NQ>
