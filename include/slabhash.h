@@ -285,6 +285,14 @@ sh_status_t sh_search_all(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uin
                           const uint64_t *d_offsets, uint32_t *d_vals_out, uint64_t d_vals_cap,
                           void *stream);
 
+/* The ranges of such an output: d_offsets[i] = d_counts[0] + ... + d_counts[i - 1] (64 bits), and
+   d_work[0] = the sum of all n counts. d_work: sh_offsets_words(n) words of 64 bits, 8-byte aligned
+   like d_offsets; the words after the first mean nothing afterwards. n < 2^32, else SH_EINVAL.
+   Asynchronous on `stream`. */
+size_t sh_offsets_words(uint64_t n);
+sh_status_t sh_search_all_offsets(const uint32_t *d_counts, uint64_t n, uint64_t *d_offsets,
+                                  uint64_t *d_work, void *stream);
+
 /* DELETEALL ("Supported Operations"; "Deletion": the whole list is processed): every live
    element with the key is deleted as sh_delete deletes one (a tombstone, or an empty slot with
    SH_TABLE_DUPLICATES). d_counts[i] (may be NULL) receives how many this call deleted. */

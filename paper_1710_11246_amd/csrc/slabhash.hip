@@ -1607,6 +1607,95 @@ __global__ __launch_bounds__(kBlock) void all_kernel(View T, const uint32_t *__r
     }
 }
 
+// Output ranges of a SEARCHALL: the exclusive prefix sum of its counts, 64 bits, in two launches.
+// A block takes kScanBlock counts, eight adjacent ones a thread: the first kernel leaves each
+// block's sum in work[1 + block], the second adds up those before its own (n / 8192 words, from
+// the caches) and scans its counts; the last block leaves the total in work[0]. Launch latency
+// bounds both: 2^18 counts take 11 us, the library calls for it before (widen, clear, scan,
+// widen, sum) 43 us.
+constexpr int kScanThreads = 1024;
+constexpr uint32_t kScanBlock = kScanThreads * 8;
+
+__device__ __forceinline__ uint64_t wave_sum64(uint64_t x)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+        x += (uint64_t)__shfl_xor((unsigned long long)x, d, 64);
+    return x;
+}
+
+// The sum of x over the block's threads; `tmp` holds one word per wavefront.
+__device__ __forceinline__ uint64_t block_sum64(uint64_t x, uint64_t *tmp)
+{
+    const uint64_t s = wave_sum64(x);
+    if (lane_id() == 0)
+        tmp[threadIdx.x >> 6] = s;
+    __syncthreads();
+    uint64_t all = 0;
+    for (int w = 0; w < kScanThreads / 64; ++w)
+        all += tmp[w];
+    __syncthreads();
+    return all;
+}
+
+template <bool Write>
+__global__ __launch_bounds__(kScanThreads) void offsets_kernel(const uint32_t *__restrict__ counts,
+                                                               uint64_t n,
+                                                               uint64_t *__restrict__ offsets,
+                                                               uint64_t *__restrict__ work)
+{
+    __shared__ uint64_t tmp[kScanThreads / 64];
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
+    const uint64_t i0 = (uint64_t)blockIdx.x * kScanBlock + tid * 8;
+    uint32_t c[8];
+    uint64_t mine = 0;
+    const bool wide = (reinterpret_cast<uintptr_t>(counts) & 15u) == 0 && i0 + 8 <= n;
+    if (wide) {
+        const uint4 a = *reinterpret_cast<const uint4 *>(counts + i0);
+        const uint4 b = *reinterpret_cast<const uint4 *>(counts + i0 + 4);
+        c[0] = a.x, c[1] = a.y, c[2] = a.z, c[3] = a.w;
+        c[4] = b.x, c[5] = b.y, c[6] = b.z, c[7] = b.w;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            c[e] = i0 + e < n ? counts[i0 + e] : 0u;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        mine += c[e];
+    if constexpr (!Write) {
+        const uint64_t sum = block_sum64(mine, tmp);
+        if (tid == 0)
+            work[1 + blockIdx.x] = sum;
+    } else {
+        uint64_t before = 0;
+        for (uint32_t b = tid; b < blockIdx.x; b += kScanThreads)
+            before += work[1 + b];
+        before = block_sum64(before, tmp);
+        uint64_t incl = mine; // over the wavefront's lanes
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint64_t t = (uint64_t)__shfl_up((unsigned long long)incl, d, 64);
+            if (lane >= (uint32_t)d)
+                incl += t;
+        }
+        if (lane == 63)
+            tmp[wv] = incl;
+        __syncthreads();
+        for (uint32_t w = 0; w < wv; ++w)
+            before += tmp[w];
+        uint64_t at = before + incl - mine;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (i0 + e < n)
+                offsets[i0 + e] = at;
+            at += c[e];
+        }
+        if (blockIdx.x == gridDim.x - 1 && tid == kScanThreads - 1)
+            work[0] = at;
+    }
+}
+
 // SlabAlloc on its own ("Dynamic memory allocation"): requests 64 w .. 64 w + 63 of n belong to
 // wavefront w, which serves them together (wave_alloc_many) from its resident block. The
 // wavefronts partition the pool: wavefront w starts in block (w / 32) mod (blocks) at bitmap
@@ -2569,6 +2658,24 @@ sh_status_t sh_search_all(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uin
         return SH_OK;
     return launch_all(t, false, d_keys, n, d_counts, d_offsets, d_vals_out,
                       d_vals_out ? d_vals_cap : 0, stream);
+}
+
+size_t sh_offsets_words(uint64_t n) { return 1 + (size_t)((n + kScanBlock - 1) / kScanBlock); }
+
+sh_status_t sh_search_all_offsets(const uint32_t *d_counts, uint64_t n, uint64_t *d_offsets,
+                                  uint64_t *d_work, void *stream)
+{
+    if (n >= (1ull << 32) || !d_work || (n && (!d_counts || !d_offsets)) ||
+        ((reinterpret_cast<uintptr_t>(d_offsets) | reinterpret_cast<uintptr_t>(d_work)) & 7u))
+        return SH_EINVAL;
+    // (no counts: one block that leaves a total of 0)
+    const dim3 grid(n ? (uint32_t)((n + kScanBlock - 1) / kScanBlock) : 1u);
+    if (n > kScanBlock)
+        hipLaunchKernelGGL(offsets_kernel<false>, grid, dim3(kScanThreads), 0, S(stream), d_counts,
+                           n, d_offsets, d_work);
+    hipLaunchKernelGGL(offsets_kernel<true>, grid, dim3(kScanThreads), 0, S(stream), d_counts, n,
+                       d_offsets, d_work);
+    return check_launch();
 }
 
 sh_status_t sh_delete_all(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_t *d_counts,

@@ -88,6 +88,8 @@ _SIGS = {
     "sh_flush": ([_P, _U32, _U32, _P], ctypes.c_int),
     "sh_alloc_slabs": ([_P, _U64, _P, _P], ctypes.c_int),
     "sh_search_all": ([_P, _P, _U64, _P, _P, _P, _U64, _P], ctypes.c_int),
+    "sh_offsets_words": ([_U64], _SZ),
+    "sh_search_all_offsets": ([_P, _U64, _P, _P, _P], ctypes.c_int),
     "sh_super_block_bytes": ([_U32], _SZ),
     "sh_add_super_block": ([_P, _P, _SZ, _P], ctypes.c_int),
     "sh_delete_all": ([_P, _P, _U64, _P, _P], ctypes.c_int),
@@ -277,6 +279,17 @@ def sh_search_all(t, keys: torch.Tensor, counts: torch.Tensor, offsets=None, val
     v = _dev(vals, "vals", _U32_TYPES, None, allow_none=True)
     cap = vals.numel() if vals is not None else 0
     _check("sh_search_all", lib().sh_search_all(t, k, n, c, o, v, cap, _stream(stream)))
+
+
+def sh_search_all_offsets(counts: torch.Tensor, offsets: torch.Tensor, stream=None) -> torch.Tensor:
+    """offsets (int64) = the exclusive prefix sum of counts; returns the work words (int64), the
+    first of which is the sum of all counts."""
+    n = counts.numel()
+    work = torch.empty(int(lib().sh_offsets_words(n)), dtype=torch.int64, device=counts.device)
+    _check("sh_search_all_offsets", lib().sh_search_all_offsets(
+        _dev(counts, "counts", _U32_TYPES), n, _dev(offsets, "offsets", (torch.int64,), n),
+        work.data_ptr(), _stream(stream)))
+    return work
 
 
 def sh_delete_all(t, keys: torch.Tensor, counts=None, stream=None) -> None:
@@ -646,11 +659,15 @@ class SlabHash:
         n = keys.numel()
         counts = torch.empty(n, dtype=torch.int32, device=keys.device)
         sh_search_all(self.handle, keys, counts, stream=stream)
-        c64 = counts.to(torch.int64)
-        offsets = torch.zeros(n, dtype=torch.int64, device=keys.device)
-        if n > 1:
-            offsets[1:] = torch.cumsum(c64[:-1], 0)
-        total = int(c64.sum().item()) if n else 0
+        offsets = torch.empty(n, dtype=torch.int64, device=keys.device)
+        work = sh_search_all_offsets(counts, offsets, stream)
+        if stream is None or _stream(stream) == _current_stream():
+            total = int(work[0])
+        else:  # the total is there once the call's own stream has passed it
+            if not isinstance(stream, torch.cuda.Stream):
+                stream = torch.cuda.ExternalStream(int(stream))
+            with torch.cuda.stream(stream):
+                total = int(work[0])
         vals = torch.empty(max(total, 1), dtype=torch.int32, device=keys.device)
         sh_search_all(self.handle, keys, counts, offsets, vals[:total] if total else vals[:1],
                       stream=stream)
