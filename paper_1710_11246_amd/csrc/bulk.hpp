@@ -634,9 +634,11 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 //                (One new pair is swapped in as it is.)
 //   new values   each replaced slot is swapped from what it holds now, key unchanged.
 //
-// What loses a swap to another kernel's update, and what finds no empty slot in the base slab, is
-// listed for the plain kernel, which runs next. A lock is held for the time of two memory round
-// trips by a wavefront that waits for nothing else meanwhile.
+// What a list of one slab has no room for goes to a new slab, whole before it is linked (left to
+// the plain kernel, where a wavefront adds one slab a round, the 2500 such pairs of 2^22 took
+// 17 us). What loses a swap to another kernel's update, and the inserts into longer lists, are
+// listed for the plain kernel, which runs next. A lock is held for the time of two or three memory
+// round trips by a wavefront that waits for nothing else meanwhile.
 //
 // One swap a slab instead of one a pair, and stores of whole runs of slots: 2^22 random swaps
 // take 158 us on this memory, swaps of 19 adjacent slots 49 us, stores of them 18 us.
@@ -690,6 +692,49 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
             A.later[at] = pos;
     };
     auto half_of = [&](uint64_t m) { return (uint32_t)(m >> hshift); };
+    // A new slab for the pairs of the half's lanes that say so, linked to the slab whose last word
+    // is `last`; true for the lanes whose pair is in the table then. The slab is taken from the
+    // table's own pool with one try per bitmap word, and a full pool, like a link lost to another
+    // kernel's, leaves the pairs to the plain kernel. Where the caller holds the slab's lock the
+    // link is not lost: no one else sees the slab full.
+    auto add_slab = [&](uint64_t *last, bool over, uint64_t pair, uint32_t seed) {
+        const uint32_t om = half_of(ballot(over));
+        const uint32_t words = T.nblk * 64, place = (uint32_t)__popc(om & below);
+        uint32_t idx = kEmpty, lk = 0;
+        if (om && slot == 0 && words) {
+            uint32_t at = __umulhi(seed, words);
+            for (int tries = 0; tries < 8 && idx == kEmpty; ++tries) {
+                const uint32_t bit = seed & 31u;
+                if (!((or32(T.bitmap + at, 1u << bit) >> bit) & 1u))
+                    idx = at * 32 + bit;
+                seed = mix32(seed);
+                at = at + 1 == words ? 0u : at + 1;
+            }
+        }
+        idx = (uint32_t)__shfl((int)idx, (int)hshift, 64);
+        const bool put = over && idx != kEmpty && place < 31;
+        uint64_t *fresh = pool_slab(T, idx != kEmpty ? idx : 0u) + place;
+        if (put)
+            __hip_atomic_store(gmem(fresh), pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" ::: "memory");
+        wait_vm_all(); // the pairs, and the stores before them, come before the link
+        asm volatile("" ::: "memory");
+        if (idx != kEmpty && slot == 0)
+            lk = cas32(reinterpret_cast<uint32_t *>(last) + 1, kEmpty, idx);
+        const bool linked = (uint32_t)__shfl((int)lk, (int)hshift, 64) == kEmpty;
+        if (!linked) {
+            // a free slab is all ones
+            if (put)
+                __hip_atomic_store(gmem(fresh), kEmptyPair, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("" ::: "memory");
+            wait_vm_all();
+            asm volatile("" ::: "memory");
+            if (idx != kEmpty && slot == 0)
+                slab_free(T, idx);
+        }
+        return put && linked;
+    };
     constexpr int kRowLoads = 8;
     uint64_t w[kRowLoads];
     auto fetch_rows = [&](uint32_t r0) {
@@ -821,6 +866,8 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                         to[u] = place;
                         out[u] = inverse_ballot(firsts) ? 2u : 1u;
                     }
+                    else if (first && (ev >> 31) && !locked)
+                        to[u] = inverse_ballot(firsts) ? 34 : 33; // a list of one full slab
                     if (inverse_ballot(dups))
                         out[u] = 4u + (inverse_ballot(lasts) ? 1u : 0u); // as the first's, below
                     fresh[u] = nm ? (uint32_t)__popc(nm) : 0u;
@@ -843,6 +890,11 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                                            __HIP_MEMORY_SCOPE_AGENT);
                     if (no)
                         fresh[u] = 0;
+                    if (ballot(to[u] > 32)) {
+                        const bool over = to[u] > 32 && !no;
+                        if (add_slab(global(u, 31), over, pr[u], mix32(b0 + row_of(u))))
+                            out[u] = to[u] - 32;
+                    }
                 }
                 // the stores have reached memory before the locks open
                 asm volatile("" ::: "memory");

@@ -11,6 +11,7 @@ import torch
 from paper_1710_11246_amd import slabhash as S
 from paper_1710_11246_amd import workload as W
 
+import host_walk as HW
 from test_gpu_parity import assert_same_table
 
 pytestmark = pytest.mark.gpu
@@ -210,11 +211,13 @@ def test_insert_leaves_full_slabs_to_the_plain_kernel(oracle_mod, pool_blocks):
         assert bad > 0 and s1["error_word"] == S.SH_ERR_POOL_EXHAUSTED
 
 
-def test_two_bulk_inserts_and_plain_inserts_at_once():
-    """Two streams insert the same keys by the bulk form while a third inserts half of them in
-    plain batches: one insert of each key is new, every other replaces, no key enters twice."""
-    say("case: bulk and plain inserts on three streams")
-    n, B = 1 << 19, 30011
+@pytest.mark.parametrize("B,bulks", [(41000, 2), (20200, 1)])
+def test_bulk_and_plain_inserts_at_once(B, bulks):
+    """Two streams insert the same keys while a third inserts half of them in small plain batches:
+    one insert of each key is new, every other replaces, no key enters twice. 13 keys a bucket
+    with both streams' inserts in the bulk form, and 26, so that lists grow, with one's."""
+    say("case: bulk and plain inserts on three streams", B)
+    n = 1 << 19
     t, _, _ = table(5, n, B)
     k = torch.from_numpy(W.distinct_keys(29, 0, n).view(np.int32)).cuda()
     perm = torch.randperm(n, device="cuda")
@@ -229,9 +232,9 @@ def test_two_bulk_inserts_and_plain_inserts_at_once():
         st3 = torch.full((n // 2,), 9, dtype=torch.uint8, device="cuda")
         ss = [torch.cuda.Stream() for _ in range(3)]
         torch.cuda.synchronize()
+        done = 0
         for (kk, vv), w, st, s in zip(sets, works, sts, ss):
-            # (the third call's count would send the second to the plain form: the table's own
-            # bound on its contents grows with every call, so both start from few keys a bucket)
+            done += S.sh_bulk_bytes(t.handle, S.SH_OP_INSERT, n) > 0
             code = S.lib().sh_insert_bulk(t.handle, kk.data_ptr(), vv.data_ptr(), n,
                                           st.data_ptr(), w.data_ptr(), nb, s.cuda_stream)
             assert code == S.SH_OK
@@ -239,6 +242,7 @@ def test_two_bulk_inserts_and_plain_inserts_at_once():
             S.sh_insert(t.handle, part[0][i:i + (1 << 15)], part[1][i:i + (1 << 15)],
                         st3[i:i + (1 << 15)], ss[2])
         torch.cuda.synchronize()
+        assert done == bulks
         s1 = t.stats()
         assert s1["live"] == n and s1["violations"] == 0 and s1["error_word"] == 0
         new = torch.zeros(n, dtype=torch.int32, device="cuda")
@@ -253,7 +257,7 @@ def test_two_bulk_inserts_and_plain_inserts_at_once():
         ok = (d == 1) | (d == 2)
         ok[: n // 2] |= d[: n // 2] == 3
         assert bool((f == 1).all()) and bool(ok.all())
-        t.dump()
+        HW.check_structure(t)
 
 
 def test_where_the_plain_form_serves():
