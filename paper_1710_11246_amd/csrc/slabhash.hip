@@ -545,10 +545,9 @@ __device__ __forceinline__ void slab_free(const View &T, uint32_t idx)
 //   2. decide: the ops are taken in lane order, a pair per step. The wavefront votes on each
 //      slab for the op's key (and, for inserts, for empty slots). The op's slot is the slot
 //      holding the key, else (inserts) the first empty slot, else slot 31, which holds the
-//      next-slab index. On key-value slabs each op receives its half of the votes in its own
-//      lane and decides there, fetching the one word it needs (the value at its key, or the
-//      next index) from the slab lane that holds it; on key-only slabs the target lane writes
-//      the outcome to the op's cell in LDS. The outcome: found (with the value), a swap to
+//      next-slab index. Each op receives its half of the votes in its own lane and decides
+//      there, fetching the one word it needs (the value at its key, or the next index) from the
+//      slab lane that holds it. The outcome: found (with the value), a swap to
 //      record (insert into the empty slot, replace the key's value, tombstone the key; with the
 //      observed value), move on to the next slab (with its index), end of list, or a new slab
 //      needed.
@@ -568,17 +567,14 @@ struct Counters {
     uint32_t rounds, cas_lost, allocs, link_lost;
 };
 
-// Outcome codes written by a target lane (bits 8.. of the message's high word; bits 0..7 hold
-// the target slot).
+// Outcome codes (bits 8.. of an outcome's high word; bits 0..7 hold the target slot or entry).
 enum : uint32_t { kMsgFound = 1, kMsgEnd = 2, kMsgMove = 3, kMsgGrow = 4, kMsgSwapIns = 5,
                   kMsgSwapRep = 6, kMsgSwapDel = 7 };
 
-// Per-wavefront LDS: cursor slab index, key and op kind of each op, and each op's outcome cell.
+// Per-wavefront LDS: cursor slab and key of each op.
 struct WaveLds {
     uint64_t p[64]; // each op's cursor slab (its address)
-    uint64_t msg[64];
     uint32_t key[64];
-    uint32_t op[64];
 };
 
 // The inputs of one chunk, one op per lane (lanes past the chunk's end hold no op).
@@ -677,6 +673,75 @@ __device__ __forceinline__ uint64_t decide_kv(const uint64_t (&pre)[NQ], uint64_
     return ((uint64_t)((code << 8) | tslot) << 32) | payload;
 }
 
+// The decide step on key-only slabs: two entries per word (entry 2 s in the low half of word s,
+// 2 s + 1 in the high half), so two key votes per slab and for updates two empty votes; otherwise as
+// decide_kv. Found keys are their own values, so the one word an op may need is the next index.
+// (Deciding in each op's own lane takes about 14 vector instructions per op pair where target
+// lanes that wrote their outcomes to LDS took some 50: 500,000 searches of 10^6 keys in 27,001
+// buckets 18.8 -> 14.9 us, 10^6 inserts, which race for slots, 109 -> 103 us.)
+template <int K, bool Dup, int NQ>
+__device__ __forceinline__ uint64_t decide_ko(const uint64_t (&pre)[NQ], uint64_t todo,
+                                              const WaveLds &L, uint32_t op, uint32_t key)
+{
+    constexpr bool kHasIns = (K == kInsert || K == kMixed);
+    const uint32_t lane = lane_id();
+    const uint32_t half = lane >> 5;
+    // this lane's op: key votes of the low and the high entries, empty votes
+    uint32_t klo = 0, khi = 0, elo = 0, ehi = 0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (!((todo >> (2 * q)) & 3ull))
+            continue;
+        const uint32_t lo = (uint32_t)pre[q];
+        uint32_t hi = (uint32_t)(pre[q] >> 32);
+        // keep `hi` a 32-bit register value, so tests on it stay 32-bit compares
+        asm("" : "+v"(hi));
+        const uint32_t kq = L.key[2 * q + half];
+        auto hand = [&](uint32_t &x, uint64_t m) {
+            x = wl(x, 2 * q, (uint32_t)m);
+            x = wl(x, 2 * q + 1, (uint32_t)(m >> 32));
+        };
+        hand(klo, ballot(lo == kq));
+        hand(khi, ballot(hi == kq));
+        if constexpr (kHasIns) {
+            hand(elo, ballot(lo == kEmpty));
+            hand(ehi, ballot(hi == kEmpty));
+        }
+    }
+    // the next index, word 31's high half
+    const uint32_t src = ((lane & 1u) * 32u + 31u) * 4u;
+    uint32_t next = 0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const uint32_t h = (uint32_t)__builtin_amdgcn_ds_bpermute(
+            (int)src, (int)(uint32_t)(pre[q] >> 32));
+        if (inverse_ballot(3ull << (2 * q)))
+            next = h;
+    }
+    const bool ins = (K == kInsert) || (K == kMixed && op == (uint32_t)kInsert);
+    const uint32_t kv = (klo | khi) & (uint32_t)kSlotMask, ev = (elo | ehi) & (uint32_t)kSlotMask;
+    const bool by_key = !(Dup && ins) && kv != 0u;
+    const bool by_empty = !by_key && ins && ev != 0u;
+    // the first entry in order that decides: of a word, the low one first
+    const uint32_t word = (uint32_t)__builtin_ctz((by_key ? kv : ev) | 0x80000000u);
+    const uint32_t low = ((by_key ? klo : elo) >> word) & 1u;
+    uint32_t code, tslot = 2 * word + 1 - low, payload = key;
+    if (by_key) {
+        code = (K == kSearch) ? kMsgFound : ((K == kDelete) ? kMsgSwapDel : kMsgSwapRep);
+        if constexpr (K == kMixed)
+            code = (op == (uint32_t)kSearch)
+                       ? kMsgFound
+                       : ((op == (uint32_t)kDelete) ? kMsgSwapDel : kMsgSwapRep);
+    } else if (by_empty) {
+        code = kMsgSwapIns;
+        payload = ev; // with duplicates empty entries need not be a suffix
+    } else {
+        code = next != kEmpty ? kMsgMove : (ins ? kMsgGrow : kMsgEnd);
+        payload = next;
+    }
+    return ((uint64_t)((code << 8) | tslot) << 32) | payload;
+}
+
 // One chunk of up to 2 NQ ops (lane l < count holds op i, with inputs `c`) on table T,
 // processed in rounds until every op has finished (see the description above). NQ is the
 // number of op pairs, and so the length of each round's straight run of loads.
@@ -694,9 +759,6 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
     constexpr bool kPrefill = !Dup && !KO;
     const uint32_t lane = lane_id();
     const uint32_t half = lane >> 5, slot = lane & 31;
-    const bool is31 = slot == 31;
-    const uint32_t below = (1u << slot) - 1u; // slots of my half below mine
-    const uint32_t hshift = lane & 32;
     const bool in = lane < count;
     const uint32_t key = c.key, val = c.val, op = c.op;
     // key-only slabs reserve a second key, the deleted-entry marker
@@ -707,8 +769,6 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
     const bool act = in && !reserved && op <= 2;
     const uint32_t bkt = act ? bucket_of(T, key) : 0u;
     L.key[lane] = key;
-    if constexpr (K == kMixed && KO)
-        L.op[lane] = op;
 
     uint32_t rv = kEmpty, rs = 0; // this lane's results
     uint32_t loc = kEmpty;        // this lane's cursor
@@ -746,79 +806,7 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
         if constexpr (!KO) {
             outcome = decide_kv<K, Dup, NQ, Locks>(pre, todo, L, op);
         } else {
-            // Key-only slabs (two entries per lane, entries 2 slot in lo and 2 slot + 1 in hi):
-            // the target lane of each op writes the op's outcome to the op's LDS cell.
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                if (!((todo >> (2 * q)) & 3ull))
-                    continue;
-                const uint64_t w = pre[q];
-                const uint32_t lo = (uint32_t)w;
-                uint32_t hi = (uint32_t)(w >> 32);
-                // keep `hi` a 32-bit register value, so tests on it stay 32-bit compares
-                asm("" : "+v"(hi));
-                const uint32_t kq = L.key[2 * q + half];
-                // votes come straight from the compares (slot 31 holds the next index)
-                const uint64_t mlo_m = ballot(lo == kq) & kSlotLanes;
-                const uint64_t mhi_m = ballot(hi == kq) & kSlotLanes;
-                const bool mlo = inverse_ballot(mlo_m);
-                const bool mhi = inverse_ballot(mhi_m);
-                const bool match = mlo || mhi;
-                const uint32_t kh = (uint32_t)((mlo_m | mhi_m) >> hshift); // my half's key votes
-                // the op's entry is the first match of the slab (with unique keys the only one)
-                const bool is_key = Dup ? (match && (kh & below) == 0u) : match;
-                const uint32_t kslot = mlo ? 2 * slot : 2 * slot + 1;
-                bool ins = (K == kInsert);
-                uint32_t code_key = (K == kSearch) ? kMsgFound
-                                                   : ((K == kDelete) ? kMsgSwapDel : kMsgSwapRep);
-                if constexpr (K == kMixed) {
-                    const uint32_t oq = L.op[2 * q + half];
-                    ins = oq == kInsert;
-                    code_key = (oq == kSearch) ? kMsgFound
-                                               : ((oq == kDelete) ? kMsgSwapDel : kMsgSwapRep);
-                }
-                bool target;
-                uint32_t code, tslot = slot;
-                uint32_t empties = 0;
-                if constexpr (kHasIns) {
-                    const uint64_t elo_m = ballot(lo == kEmpty) & kSlotLanes;
-                    const uint64_t ehi_m = ballot(hi == kEmpty) & kSlotLanes;
-                    const bool elo = inverse_ballot(elo_m);
-                    const bool ehi = inverse_ballot(ehi_m);
-                    const bool is_empty = elo || ehi;
-                    const uint32_t eh = (uint32_t)((elo_m | ehi_m) >> hshift);
-                    empties = eh;
-                    const bool first_empty = ins && is_empty && (eh & below) == 0u;
-                    const bool tail = is31 && (!ins || eh == 0u);
-                    // with duplicates an insert takes the first empty entry whatever keys it
-                    // meets
-                    const bool hit = Dup ? (is_key && !ins) : is_key;
-                    const uint32_t khe = (Dup && ins) ? 0u : kh;
-                    target = hit || (khe == 0u && (first_empty || tail));
-                    code = hit ? code_key
-                               : (first_empty ? kMsgSwapIns
-                                              : (hi != kEmpty ? kMsgMove
-                                                              : (ins ? kMsgGrow : kMsgEnd)));
-                    if (hit)
-                        tslot = kslot;
-                    else if (first_empty)
-                        tslot = elo ? 2 * slot : 2 * slot + 1;
-                } else {
-                    target = is_key || (kh == 0u && is31);
-                    code = is_key ? code_key : (hi != kEmpty ? kMsgMove : kMsgEnd);
-                    if (is_key)
-                        tslot = kslot;
-                }
-                // the payload: the key itself when found (a search reports it as the value),
-                // the next index, or for an insert into an empty entry with duplicates, the
-                // lanes of the slab that showed an empty entry (they need not be a suffix)
-                const uint32_t payload =
-                    (Dup && code == kMsgSwapIns) ? empties : (is_key ? kq : hi);
-                if (target)
-                    L.msg[2 * q + half] = ((uint64_t)((code << 8) | tslot) << 32) | payload;
-            }
-            __builtin_amdgcn_wave_barrier();
-            outcome = L.msg[lane];
+            outcome = decide_ko<K, Dup, NQ>(pre, todo, L, op, key);
         }
         // ---- 3. act on the outcome ----
         const bool mine = (todo >> lane) & 1;
