@@ -754,7 +754,6 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                           uint32_t count, uint32_t flags)
 {
     constexpr bool kCoherent = (K != kSearch);
-    constexpr bool kHasIns = (K == kInsert || K == kMixed);
     // unique-key pair inserts write their pair into a new tail slab before linking it
     constexpr bool kPrefill = !Dup && !KO;
     const uint32_t lane = lane_id();
