@@ -74,7 +74,7 @@ def chain_visits(occ: np.ndarray, m: int = 31) -> float:
 
 
 def op_bytes(kind: str, n: int, v_hit: float, v_miss: float, new_slabs: int = 0,
-             mix=None) -> float:
+             mix=None, slabs: int = 0) -> float:
     """Algorithmic bytes of one launch of n ops, with v_hit / v_miss the mean slabs a walk to a
     present key / to the end of a list reads (256 bytes each):
       search:  4 (key) + 256 v + 4 (value) + 1 (found);
@@ -85,7 +85,14 @@ def op_bytes(kind: str, n: int, v_hit: float, v_miss: float, new_slabs: int = 0,
       mixed:   per op 1 (op) + 4 (key) + 4 (value in) + 4 (value out) + 1 (status); slabs
                v_miss for inserts and absent searches, v_hit for deletes and present searches;
                64 per insert or delete; 8 / 31 per insert for new slabs (amortised).
-    mix = (inserts, deletes, present searches, absent searches) of a mixed batch."""
+    mix = (inserts, deletes, present searches, absent searches) of a mixed batch.
+    slabs > 0: the call takes the bulk form, which reads each of that many slabs once:
+      search:  9 per op + 256 per slab of the table;
+      insert:  9 per op + 512 per base slab (read, and its pairs written) + 264 per new slab."""
+    if slabs and kind == "insert":
+        return 9.0 * n + 512.0 * slabs + 264.0 * new_slabs
+    if slabs:
+        return 9.0 * n + 256.0 * slabs
     if kind == "search_hit":
         return n * (4 + 4 + 1) + 256.0 * v_hit * n
     if kind == "search_miss":
@@ -100,6 +107,14 @@ def op_bytes(kind: str, n: int, v_hit: float, v_miss: float, new_slabs: int = 0,
         return (n * (1 + 4 + 4 + 4 + 1) + 256.0 * ((ni + nm) * v_miss + (nd + nh) * v_hit)
                 + 64.0 * (ni + nd) + 8.0 * ni / 31)
     raise ValueError(kind)
+
+
+def bulk_forms(handle, n: int) -> dict:
+    """Which calls of n ops take the bulk form on this table, which must be empty."""
+    from paper_1710_11246_amd import slabhash as S
+    search = S.sh_bulk_bytes(handle, S.SH_OP_SEARCH, n) > 0
+    return {"build": S.sh_bulk_bytes(handle, S.SH_OP_INSERT, n) > 0, "search_hit": search,
+            "search_miss": search}
 
 
 def make_inputs(util: float, seed: int = 11):
@@ -567,6 +582,7 @@ def sweep_utilisation(wl0, n_seeds: int = 5, reps: int = 3) -> dict:
         for u, Bu in sorted(B_FOR_UTIL.items()):
             tu = S.SlabHash(Bu, S.pool_slabs_bound(N_KEYS), wl.hash_a, wl.hash_b)
             res = {nm: [] for nm in names}
+            bulk = bulk_forms(tu.handle, N_KEYS)
             for rep in range(reps + 1):
                 tu.reset()
                 e = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
@@ -595,7 +611,9 @@ def sweep_utilisation(wl0, n_seeds: int = 5, reps: int = 3) -> dict:
                          "search_miss": "search_miss"}
                 per[u]["frac_hbm"] = {
                     nm: round(op_bytes(kinds[nm], N_KEYS, v_hit, v_miss,
-                                       new_slabs=s_u["pool_allocated"] if nm == "build" else 0)
+                                       new_slabs=s_u["pool_allocated"] if nm == "build" else 0,
+                                       slabs=bulk[nm] * (Bu if nm == "build"
+                                                         else s_u["slabs_total"]))
                               / (float(np.median(res[nm])) * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)
                     for nm in names}
                 per[u]["slabs_per_miss"] = round(v_miss, 4)
@@ -762,6 +780,7 @@ def measure_hbm_resident(log2n: int = 26, util: float = 0.6, reps: int = 3,
     fm = torch.empty(n, dtype=torch.uint8, device="cuda")
     names = ("build", "search_hit", "search_miss")
     res = {k: [] for k in names}
+    bulk = bulk_forms(t.handle, n)
     for rep in range(reps + 1):
         t.reset()
         e = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
@@ -788,9 +807,12 @@ def measure_hbm_resident(log2n: int = 26, util: float = 0.6, reps: int = 3,
     assert int(viol.item()) == 0 and int(cnt.item()) == n
     v_hit = chain_visits(c[:, 0].astype(np.int64) + c[:, 1]) / n
     v_miss = float(c[:, 2].mean())
-    bytes_l = {"build": op_bytes("insert", n, v_hit, v_miss, new_slabs=su["pool_allocated"]),
-               "search_hit": op_bytes("search_hit", n, v_hit, v_miss),
-               "search_miss": op_bytes("search_miss", n, v_hit, v_miss)}
+    bytes_l = {"build": op_bytes("insert", n, v_hit, v_miss, new_slabs=su["pool_allocated"],
+                                 slabs=bulk["build"] * B),
+               "search_hit": op_bytes("search_hit", n, v_hit, v_miss,
+                                      slabs=bulk["search_hit"] * su["slabs_total"]),
+               "search_miss": op_bytes("search_miss", n, v_hit, v_miss,
+                                       slabs=bulk["search_miss"] * su["slabs_total"])}
     traffic_ok = source_sha() == TRAFFIC_SRC_SHA
     out = {"workload": "bulk build of 2^%d uniform uint32 keys, then 2^%d all-hit and 2^%d "
                        "all-miss searches" % (log2n, log2n, log2n),
@@ -1165,6 +1187,7 @@ def main():
     table = S.SlabHash(B, pool, wl.hash_a, wl.hash_b)
     if args.waves_per_cu:
         table.set_launch(args.waves_per_cu)
+    bulk = bulk_forms(table.handle, N_KEYS)
     h = table.handle
     dev = "cuda"
     keys, vals = S.to_dev(wl["keys"]), S.to_dev(wl["vals"])
@@ -1283,12 +1306,16 @@ def main():
     util = 8.0 * stats_built["live"] / (256.0 * stats_built["slabs_total"])
 
     # Algorithmic bytes per launch (op_bytes): inputs and outputs once, the 256-byte slabs the
-    # walks read, 64 bytes per swap and 8 per new slab; a reset writes the table's header and
+    # walks read (a call in the bulk form: each slab once), 64 bytes per swap and 8 per new slab
+    # (in the bulk form each base slab written once); a reset writes the table's header and
     # base slabs and the pool slabs in use, and reads then zeroes the allocator bitmaps.
     bytes_l = {
-        "build": op_bytes("insert", N_KEYS, v_hit, v_miss, new_slabs=new_slabs),
-        "search_hit": op_bytes("search_hit", N_KEYS, v_hit, v_miss),
-        "search_miss": op_bytes("search_miss", N_KEYS, v_hit, v_miss),
+        "build": op_bytes("insert", N_KEYS, v_hit, v_miss, new_slabs=new_slabs,
+                          slabs=bulk["build"] * B),
+        "search_hit": op_bytes("search_hit", N_KEYS, v_hit, v_miss,
+                               slabs=bulk["search_hit"] * stats_built["slabs_total"]),
+        "search_miss": op_bytes("search_miss", N_KEYS, v_hit, v_miss,
+                                slabs=bulk["search_miss"] * stats_built["slabs_total"]),
         "mixed": op_bytes("mixed", MIX_BATCH, v_hit, v_miss, mix=(n_ins, n_del, n_hit, n_miss)),
         "reset": float(4096 + 256 * B + 256 * stats_end["pool_allocated"] +
                        2 * 256 * (table.params.pool_slabs // 2048)),

@@ -56,3 +56,10 @@ def test_op_bytes_model():
     # the benchmark's build at 60% utilisation: 2^22 inserts
     b = bench.op_bytes("insert", 1 << 22, 1.0006, 1.0052, new_slabs=20000)
     assert abs(b / (1 << 22) - (73 + 256 * 1.0052)) < 0.05
+
+
+def test_op_bytes_of_the_bulk_form():
+    """Each slab once: 9 bytes per op, and per slab 256 (searches) or 512 (inserts)."""
+    assert bench.op_bytes("search_hit", 100, 1.5, 1.5, slabs=7) == 900 + 256 * 7
+    assert bench.op_bytes("search_miss", 100, 1.5, 1.5, slabs=7) == 900 + 256 * 7
+    assert bench.op_bytes("insert", 100, 1.5, 1.5, new_slabs=2, slabs=7) == 900 + 512 * 7 + 528
