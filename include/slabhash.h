@@ -254,10 +254,11 @@ sh_status_t sh_search(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_
    (SH_OP_SEARCH or SH_OP_INSERT) on `stream` needs now, or 0 where the plain form serves it:
    small batches, fewer than six operations per bucket, inserts that the base slabs would have no
    room for, inserts into tables with flags and into tables of a multi-table object, tables with a
-   launch shape set by sh_set_launch, and streams that are being captured. The calls themselves take the plain form where there is no
-   bulk form or the workspace is missing (NULL) or too small. The workspace belongs to one call:
-   its contents need not be set before and mean nothing after, and calls that may overlap need one
-   each. It is at most 1.1 GB: longer batches are taken in pieces of 2^26. */
+   launch shape set by sh_set_launch, and streams that are being captured. The calls themselves
+   take the plain form where there is no bulk form or the workspace is missing (NULL) or too
+   small. The workspace belongs to one call: its contents need not be set before and mean nothing
+   after, and calls that may overlap need one each. It is at most 1.1 GB: longer batches are taken
+   in pieces of 2^26. */
 size_t sh_bulk_bytes(const sh_table_t *t, int kind, uint64_t n, void *stream);
 sh_status_t sh_search_bulk(sh_table_t *t, const uint32_t *d_keys, uint64_t n,
                            uint32_t *d_vals_out, uint8_t *d_found, void *d_work,
