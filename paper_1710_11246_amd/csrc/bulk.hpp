@@ -9,20 +9,23 @@
 //           gathered from every tile's run and answered there; results replace the operations.
 //   merge   each tile's results go back to the batch's order, through LDS.
 //
-// Times of the kernels (us; 217,316 buckets at 2^22 operations, 3,477,982 at 2^26):
+// Times of the kernels (us; 217,316 buckets at 2^22 operations, 3,477,982 at 2^26; searches: the
+// mean of all present and all absent):
 //
 //                     plain   bulk   of it: split   probe / insert   later   merge
-//   2^22 searches       148     66             15               40               9
-//   2^26 searches      2860   1500            190             1150             160
-//   2^22 inserts        239    122             20               71      11       6
-//   2^26 inserts       4340   2070            291             1686      56      58
+//   2^22 searches       152     71             15               43               9
+//   2^26 searches      2890   1540            200             1170             168
+//   2^22 inserts        239    114             20               72      11       6
+//   2^26 inserts       4340   2070            293             1700      19      57
 //
-// A search moves 18 bytes through the workspace besides its share of the slab, an insert 23, where
-// the plain form reads 256 bytes at random, and an insert swaps 8. Split and merge are bound by
-// their LDS traffic and the ends of their tiles' phases; probe and insert by the chain of waits of
-// a part (run starts, operations, slabs, and the swap and the stores of an insert), which other
-// parts on the same compute unit cover: three of 8 wavefronts at 2^22 operations, none at 2^26,
-// where the tiles cannot count more parts and a part's slabs fill the LDS.
+// The plain form reads 256 bytes at random per operation, and an insert swaps 8. Split and merge
+// are bound by memory at 2^26 (split moves 10 bytes per search and 18 per insert: 3.4 and 4.1 TB/s;
+// a searches' merge 12: 4.8), by the ends of their tiles' phases at 2^22. Probe and insert are
+// bound by the chain of waits of a part (run starts, operations, slabs, and the swap and the stores
+// of an insert), which other parts on the same compute unit cover: three of 8 wavefronts at 2^22
+// operations, none at 2^26, where the tiles cannot count more parts and a part's slabs fill the
+// LDS. (Slabs left out of LDS, with only their tags there and a found pair read from L2: more parts
+// per compute unit, but 2^22 searches 64 -> 73 us and 2^26 1533 -> 1762 us.)
 //
 // A run of a tile is a few operations (tile / parts), less than a cache line. Workgroups b,
 // b + 8, b + 16, ... share an XCD, so they take consecutive parts: the lines their runs share
