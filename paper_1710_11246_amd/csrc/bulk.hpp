@@ -13,13 +13,13 @@
 // mean of all present and all absent):
 //
 //                     plain   bulk   of it: split   probe / insert   later   merge
-//   2^22 searches       152     71             15               43               9
-//   2^26 searches      2890   1540            200             1170             168
+//   2^22 searches       152     69             15               41               9
+//   2^26 searches      2890   1430            200             1070             168
 //   2^22 inserts        239    114             20               72      11       6
 //   2^26 inserts       4340   2070            293             1700      19      57
 //
 // The plain form reads 256 bytes at random per operation, and an insert swaps 8. Split and merge
-// are bound by memory at 2^26 (split moves 10 bytes per search and 18 per insert: 3.4 and 4.1 TB/s;
+// are bound by memory at 2^26 (split moves 11 bytes per search and 18 per insert: 3.7 and 4.1 TB/s;
 // a searches' merge 12: 4.8), by the ends of their tiles' phases at 2^22. Probe and insert are
 // bound by the chain of waits of a part (run starts, operations, slabs, and the swap and the stores
 // of an insert), which other parts on the same compute unit cover: three of 8 wavefronts at 2^22
@@ -280,8 +280,11 @@ __global__ __launch_bounds__(kSplitThreads) void split_kernel(View T, Bulk A,
     }
     __syncthreads();
     uint32_t *out = A.key + base;
-    for (uint32_t i = tid * 4; i < total; i += kSplitThreads * 4)
+    for (uint32_t i = tid * 4; i < total; i += kSplitThreads * 4) {
         *reinterpret_cast<uint4 *>(out + i) = *reinterpret_cast<const uint4 *>(stage + i);
+        if constexpr (!Vals)
+            *reinterpret_cast<uint32_t *>(A.flag + base + i) = 0u;
+    }
     if constexpr (Vals) {
         // the values the same way (no key of an insert is left out as a repetition)
         const uint32_t *vin = vals + base;
@@ -633,8 +636,12 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
         }
         for (uint32_t q = tid; q < count; q += kThreads) {
             const uint32_t o = owner[q], at = R.shift[o & 0x7FFFu] + q0 + q;
-            A.key[at] = queue[q];
-            A.flag[at] = (uint8_t)(o >> 15);
+            const uint32_t val = queue[q];
+            A.key[at] = val;
+            // Only what the value does not tell (split has written zeros, whole lines): a run's
+            // flags are a few bytes of a line, and writing them all took 2^26 searches 96 us.
+            if (val == kEmpty && (o >> 15))
+                A.flag[at] = 1;
         }
     }
 }
@@ -1021,18 +1028,23 @@ __global__ __launch_bounds__(kSplitThreads) void merge_kernel(Bulk A, uint64_t n
         const uint2 pl = *reinterpret_cast<const uint2 *>(A.place + base + i);
         const uint32_t p[4] = {pl.x & 0xFFFFu, pl.x >> 16, pl.y & 0xFFFFu, pl.y >> 16};
         if (wide && i + 4 <= count) {
-            if (vout)
-                *reinterpret_cast<uint4 *>(vout + i) =
-                    make_uint4(val[p[0]], val[p[1]], val[p[2]], val[p[3]]);
+            uint32_t found = 0; // searches that return a value: found whatever the flag
+            if (vout) {
+                const uint4 v = make_uint4(val[p[0]], val[p[1]], val[p[2]], val[p[3]]);
+                *reinterpret_cast<uint4 *>(vout + i) = v;
+                found = (v.x != kEmpty ? 1u : 0u) | (v.y != kEmpty ? 1u << 8 : 0u) |
+                        (v.z != kEmpty ? 1u << 16 : 0u) | (v.w != kEmpty ? 1u << 24 : 0u);
+            }
             if (sout)
                 *reinterpret_cast<uint32_t *>(sout + i) =
-                    flag[p[0]] | (flag[p[1]] << 8) | (flag[p[2]] << 16) | (flag[p[3]] << 24);
+                    found | flag[p[0]] | (flag[p[1]] << 8) | (flag[p[2]] << 16) |
+                    (flag[p[3]] << 24);
         } else {
             for (uint32_t e = 0; e < 4 && i + e < count; ++e) {
                 if (vout)
                     vout[i + e] = val[p[e]];
                 if (sout)
-                    sout[i + e] = flag[p[e]];
+                    sout[i + e] = flag[p[e]] | (vout && val[p[e]] != kEmpty ? 1 : 0);
             }
         }
     }

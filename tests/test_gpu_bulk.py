@@ -329,3 +329,18 @@ def test_where_the_plain_form_serves():
         torch.cuda.synchronize()
         assert bool((v == ~k).all())
     assert ctypes.sizeof(ctypes.c_size_t) == 8
+
+
+@pytest.mark.parametrize("n,B", [((3 << 20) + 3, 100003), ((1 << 23) + 1, 300007)])
+def test_values_of_all_ones_are_found(n, B):
+    """A value that looks like an absent key's result: the flag alone tells them apart, in whole
+    groups of four and in a last one."""
+    say("case: bulk search, values all ones", n, B)
+    t, _, _ = table(41, n, B)
+    keys = torch.from_numpy(W.distinct_keys(43, 0, n).view(np.int32)).cuda()
+    held = torch.arange(n, device="cuda") % 3 != 1
+    vals = torch.where(torch.arange(n, device="cuda") % 2 == 0, -1, 7).to(torch.int32)
+    t.insert(keys[held], vals[held], status=False)
+    v, f = bulk_search(t, keys)
+    assert bool((f == held).all())
+    assert bool((v == torch.where(held, vals, -1)).all())
