@@ -10,10 +10,10 @@ uint32 support); ops, statuses and found flags are torch.uint8.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import re
-import threading
 
 import numpy as np
 import torch
@@ -145,6 +145,8 @@ def lib() -> ctypes.CDLL:
             f = getattr(l, name)
             f.argtypes = args
             f.restype = res
+        # of the HIP runtime that the library is linked with
+        l.hipThreadExchangeStreamCaptureMode.argtypes = [ctypes.POINTER(ctypes.c_int)]
         _lib = l
     return _lib
 
@@ -180,8 +182,20 @@ def _stream(stream) -> int:
     return int(stream)
 
 
-# sh_capture_begin calls of this thread that sh_capture_end has not ended
-_capturing = threading.local()
+@contextlib.contextmanager
+def _outside_captures():
+    """Lets this thread take device memory while a stream is being captured, by this thread or by
+    another one. A device allocation is refused meanwhile, and ends the capture, unless the calling
+    thread's capture mode is relaxed (2): memory taken here is no part of any capture."""
+    mode = ctypes.c_int(2)
+    exchange = lib().hipThreadExchangeStreamCaptureMode
+    if exchange(ctypes.byref(mode)) != 0:
+        raise RuntimeError("hipThreadExchangeStreamCaptureMode failed")
+    try:
+        yield
+    finally:
+        exchange(ctypes.byref(mode))
+
 
 #: No batch below these takes the bulk form (the library's own lines lie at or above them).
 _BULK_MIN = {SH_OP_SEARCH: 1 << 21, SH_OP_INSERT: 1 << 17}
@@ -197,7 +211,7 @@ def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     been enqueued. A stream that torch does not own, a capture in progress and a device without
     room take the plain form."""
     n = keys.numel()
-    if n < _BULK_MIN[kind] or getattr(_capturing, "depth", 0):
+    if n < _BULK_MIN[kind]:
         return None
     if stream is None or _stream(stream) == _current_stream():
         stream = torch.cuda.current_stream()
@@ -207,7 +221,7 @@ def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     if nbytes == 0:
         return None
     try:
-        with torch.cuda.stream(stream):
+        with torch.cuda.stream(stream), _outside_captures():
             return torch.empty(nbytes, dtype=torch.uint8, device=keys.device)
     except torch.cuda.OutOfMemoryError:
         return None
@@ -470,13 +484,11 @@ def sh_multi_graph(m, desc, nb, ops, keys, vals_in, vals_out, status) -> ctypes.
 def sh_capture_begin(stream) -> None:
     """Start capturing the work later calls enqueue on `stream` (a non-default stream)."""
     _check("sh_capture_begin", lib().sh_capture_begin(_stream(stream)))
-    _capturing.depth = getattr(_capturing, "depth", 0) + 1
 
 
 def sh_capture_end(stream) -> ctypes.c_void_p:
     """Finish the capture on `stream`; returns the graph (replay with sh_graph_launch)."""
     out = ctypes.c_void_p()
-    _capturing.depth = max(0, getattr(_capturing, "depth", 0) - 1)
     _check("sh_capture_end", lib().sh_capture_end(_stream(stream), ctypes.byref(out)))
     return out
 
