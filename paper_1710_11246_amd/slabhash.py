@@ -208,17 +208,19 @@ def sh_bulk_bytes(t, kind: int, n: int, stream=None) -> int:
 def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     """The workspace of a call's bulk form, or None for the plain form: torch memory of the
     stream that the call runs on, so that it returns to that stream's pool when the call has
-    been enqueued. A stream that torch does not own, a capture in progress and a device without
-    room take the plain form."""
+    been enqueued. A stream that torch does not own or that is being captured, and a device
+    without room, take the plain form. (The size comes first: a call without a bulk form pays for
+    one call into the library and for no Stream object.)"""
     n = keys.numel()
     if n < _BULK_MIN[kind]:
         return None
-    if stream is None or _stream(stream) == _current_stream():
+    raw = _stream(stream)
+    nbytes = lib().sh_bulk_bytes(t, kind, n, raw)
+    if nbytes == 0:
+        return None
+    if stream is None or raw == _current_stream():
         stream = torch.cuda.current_stream()
     elif type(stream) is not torch.cuda.Stream:
-        return None
-    nbytes = sh_bulk_bytes(t, kind, n, stream)
-    if nbytes == 0:
         return None
     try:
         with torch.cuda.stream(stream), _outside_captures():
