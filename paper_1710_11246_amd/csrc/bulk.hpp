@@ -670,25 +670,38 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 //
 // A bucket's inserts are lined up in LDS by counting, up to 32; the slab itself stays in
 // registers, a slot per lane, and meets the lane that holds the insert of its place in line.
-// Inserts of one key must not take two slots: each sets one of 512 bits of its bucket, and only
-// one that finds its bit set is compared with the others of its line.
+// Inserts of one key must not take two slots: each sets one of 512 bits of its bucket, and one
+// that finds its bit set, or no place, looks through the line. Where the line holds its key, one
+// of that key's inserts keeps its place for all of them: the one whose bit was clear, or else (two
+// keys share the bit) the first of the line. It is made last, so its value stays and it finds the
+// key there; a new key is new to one of the others. A popular key so costs one swap a piece and a
+// look through LDS per insert, whatever the length of its run. (Comparing the groups of each key in
+// the commit, and leaving what had no place in line to the plain kernel, took the kernel 31.7 us
+// where this takes 21.1 with every key twice, 2^18 in 40,960 buckets; 92 us and 86 more in the
+// plain kernel where this takes 71 and 9 with Zipf(0.8) keys, 2^18 in 21,845; and 71.8 us where this
+// takes 73.8 with distinct keys, 2^22 in 217,000.)
 constexpr uint32_t kSigWords = 16;
-constexpr uint32_t kInsRowBytes = kRowWords * 8 + kSigWords * 4 + 8; // LDS per bucket
+constexpr uint32_t kInsRowBytes = kRowWords * 8 + kSigWords * 4 + 12; // LDS per bucket
 
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
 {
     extern __shared__ uint64_t sm8[];
     constexpr uint32_t kThreads = NW * 64;
-    constexpr uint32_t kLater = 3; // a result beside the statuses 0, 1, 2
+    constexpr uint32_t kLater = 3; // results beside the statuses 0, 1, 2
+    constexpr uint32_t kNewOther = 4; // new to another insert of the key; this one replaced it
     constexpr uint32_t kNoLine = 0x8000u; // `line` of an insert without a place: | its result
+    // `owner`: the tile, and whether the insert's key keeps another's place in line, and whether
+    // this one is the insert that a new key is new to
+    constexpr uint32_t kRepeat = 0x8000u, kNewTo = 0x4000u, kTileOf = 0x3FFFu;
     uint64_t *pairs = sm8; // the buckets' lines
     uint32_t *sig = reinterpret_cast<uint32_t *>(pairs + ((A.span * kRowWords + 1) & ~1u));
     uint8_t *res = reinterpret_cast<uint8_t *>(sig); // 32 results per line, once the bits are done
     uint32_t *cnt = sig + A.span * kSigWords;
-    uint32_t *again = cnt + A.span; // bit i: the line's insert i found its bit set
+    uint32_t *again = cnt + A.span;  // bit i: the line's insert i found its bit set
+    uint32_t *shared = again + A.span; // bit i: it keeps its place for others of its key too
     Runs R;
-    R.first = again + A.span;
+    R.first = shared + A.span;
     R.shift = R.first + A.tiles + 1;
     uint32_t *tmp = R.shift + A.tiles;
     uint16_t *owner = reinterpret_cast<uint16_t *>(tmp + NW);
@@ -771,7 +784,6 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
     };
     fetch_rows(wv * 2); // in flight while the runs are read and summed
     const uint32_t total = load_runs<NW>(A, part, R, tmp, owner);
-    const uint32_t most = 4 * A.queue; // a part of repeated keys: the rest goes the plain way
     bool have = true;
     for (uint32_t q0 = 0; q0 < total; q0 += A.queue) {
         const uint32_t count = total - q0 < A.queue ? total - q0 : A.queue;
@@ -779,18 +791,12 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
             __syncthreads(); // the runs are there, and the last piece is done
             own_runs<NW>(A, R, q0, q0 + count, owner);
         }
-        if (q0 >= most) {
-            __syncthreads();
-            for (uint32_t i = tid & ~63u; i < count; i += kThreads) {
-                const uint32_t q = i + lane;
-                leave(q < count, q < count ? R.shift[owner[q]] + q0 + q : 0u);
-            }
-            continue;
-        }
-        for (uint32_t i = tid; i < A.span * (kSigWords + 2); i += kThreads)
+        for (uint32_t i = tid; i < A.span * (kSigWords + 3); i += kThreads)
             sig[i] = 0u; // (and the counts)
         __syncthreads();
-        for (uint32_t i = tid; i < count; i += 4 * kThreads) {
+        uint32_t look = 0; // bit j: insert tid + j * kThreads looks through its line
+        uint32_t j0 = 0;
+        for (uint32_t i = tid; i < count; i += 4 * kThreads, j0 += 4) {
             uint32_t k[4], v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -809,18 +815,52 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                     const uint32_t r = bucket_of(T, k[u]) - b0;
                     const uint32_t at = atomicAdd(&cnt[r], 1u);
                     l = kNoLine | kLater;
+                    bool looks = true;
                     if (at < 32u) {
                         pairs[r * kRowWords + at] = ((uint64_t)v[u] << 32) | k[u];
                         const uint32_t h = (k[u] * 0x9E3779B1u) >> 23;
                         const uint32_t old = atomicOr(&sig[r * kSigWords + (h >> 5)],
                                                       1u << (h & 31u));
-                        if ((old >> (h & 31u)) & 1u)
+                        looks = (old >> (h & 31u)) & 1u;
+                        if (looks)
                             atomicOr(&again[r], 1u << at);
                         l = r * 32 + at;
                     }
+                    look |= looks ? 1u << (j0 + u) : 0u;
                 }
                 line[q] = (uint16_t)l;
             }
+        }
+        __syncthreads();
+        for (; look; look &= look - 1u) {
+            const uint32_t q = tid + (uint32_t)__builtin_ctz(look) * kThreads;
+            const uint32_t l = line[q];
+            uint32_t r = l >> 5, key;
+            if (l & kNoLine) {
+                key = A.key[R.shift[owner[q]] + q0 + q];
+                r = bucket_of(T, key) - b0;
+            } else {
+                key = (uint32_t)pairs[r * kRowWords + (l & 31u)];
+            }
+            const uint32_t c = cnt[r] < 32u ? cnt[r] : 32u;
+            uint32_t is = 0; // the line's inserts of this key (a place given up in this loop
+                             // meanwhile may be missing: it is not the one that is kept)
+            for (uint32_t j = 0; j < c; j += 16)
+#pragma unroll
+                for (uint32_t i = 0; i < 16; ++i)
+                    is |= (uint32_t)pairs[r * kRowWords + j + i] == key ? 1u << (j + i) : 0u;
+            is &= c < 32u ? (1u << c) - 1u : ~0u;
+            if (!is)
+                continue; // (no place and no one to share one with)
+            const uint32_t clear = is & ~again[r];
+            const uint32_t kept = r * 32 + (uint32_t)__builtin_ctz(clear ? clear : is);
+            if (kept == l)
+                continue;
+            const uint32_t bit = 1u << (kept & 31u);
+            owner[q] |= (atomicOr(&shared[r], bit) & bit) ? kRepeat : kRepeat | kNewTo;
+            line[q] = (uint16_t)kept;
+            if (!(l & kNoLine))
+                pairs[r * kRowWords + (l & 31u)] = kEmptyPair; // gives up its place
         }
         __syncthreads();
         for (uint32_t r0 = wv * 2; r0 < nb; r0 += NW * 2 * kRowLoads) {
@@ -831,41 +871,29 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
 #pragma unroll
             for (int u0 = 0; u0 < kRowLoads; u0 += kC) {
                 uint64_t pr[kC], old[kC], want[kC];
-                uint32_t to[kC], out[kC], rep[kC]; // the slot; the result if all goes well
+                uint32_t to[kC], out[kC]; // the slot; the result if all goes well
                 uint32_t e[kC], fresh[kC];
                 auto row_of = [&](int u) { return r0 + (u0 + u) * NW * 2 + half; };
                 auto global = [&](int u, uint32_t s) {
                     return T.base + (size_t)(b0 + row_of(u)) * 32 + s;
+                };
+                auto new_to = [&](int u) { // the result of a lane's new key
+                    return (shared[row_of(u)] >> slot) & 1u ? kNewOther : 1u;
                 };
 #pragma unroll
                 for (int u = 0; u < kC; ++u) {
                     const uint64_t x = w[u0 + u];
                     const bool in = row_of(u) < nb;
                     const uint32_t c = in ? cnt[row_of(u)] : 0u;
-                    const bool has = slot < c;
-                    pr[u] = has ? pairs[row_of(u) * kRowWords + slot] : 0ull;
+                    pr[u] = slot < c ? pairs[row_of(u) * kRowWords + slot] : kEmptyPair;
                     const uint32_t key = (uint32_t)pr[u];
+                    const bool has = key != kEmpty;
                     const uint32_t ev = half_of(ballot(x == kEmptyPair));
                     const uint32_t locked = half_of(ballot(x == kLockPair));
                     e[u] = locked ? 31u : (uint32_t)__builtin_ctz(ev | 0x80000000u);
                     to[u] = 32;
                     out[u] = has ? kLater : 0u;
-                    rep[u] = lane;
                     want[u] = kEmptyPair;
-                    uint64_t dups = 0, firsts = 0, lasts = 0; // of groups of one key
-                    const uint32_t ag = in ? again[row_of(u)] : 0u;
-                    for (uint64_t m = ballot(has && ((ag >> slot) & 1u)); m; m &= m - 1) {
-                        const uint32_t j = ffs0(m);
-                        const uint64_t g = ballot(has && key == rl(key, j)) &
-                                           (0xFFFFFFFFull << (j & 32u));
-                        if (g & (g - 1)) {
-                            firsts |= g & (0 - g);
-                            dups |= g & (g - 1);
-                            lasts |= 1ull << (63 - __builtin_clzll(g));
-                            if (inverse_ballot(g))
-                                rep[u] = ffs0(g);
-                        }
-                    }
                     // keys that are there: the slots' live pairs, one after another
                     const uint64_t live = ballot(in && slot < 31 && (uint32_t)x != kEmpty);
                     if (ballot(has)) {
@@ -880,27 +908,22 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                             }
                         }
                     }
-                    const bool first = has && !inverse_ballot(dups);
-                    const uint32_t nm = half_of(ballot(first && to[u] == 32));
+                    const uint32_t nm = half_of(ballot(has && to[u] == 32));
                     const uint32_t place = e[u] + (uint32_t)__popc(nm & below);
-                    // a new key: the value stored is the first's of its group, which so is the
-                    // last to act; the group's last insert is the one that finds no key
-                    if (first && to[u] < 32)
+                    if (has && to[u] < 32) {
                         out[u] = 2;
-                    else if (first && place < 31) {
+                    } else if (has && place < 31) {
                         to[u] = place;
-                        out[u] = inverse_ballot(firsts) ? 2u : 1u;
+                        out[u] = new_to(u);
+                    } else if (has && (ev >> 31) && !locked) {
+                        to[u] = 33; // a list of one full slab
                     }
-                    else if (first && (ev >> 31) && !locked)
-                        to[u] = inverse_ballot(firsts) ? 34 : 33; // a list of one full slab
-                    if (inverse_ballot(dups))
-                        out[u] = 4u + (inverse_ballot(lasts) ? 1u : 0u); // as the first's, below
                     fresh[u] = nm ? (uint32_t)__popc(nm) : 0u;
                     if (fresh[u] > 31u - e[u])
                         fresh[u] = 31u - e[u];
-                    const bool opens = first && want[u] == kEmptyPair && to[u] == e[u];
+                    const bool opens = has && want[u] == kEmptyPair && to[u] == e[u];
                     old[u] = want[u];
-                    if (first && (opens ? to[u] < 31 : want[u] != kEmptyPair))
+                    if (has && (opens ? to[u] < 31 : want[u] != kEmptyPair))
                         old[u] = cas64(global(u, to[u]), want[u],
                                        opens && fresh[u] > 1 ? kLockPair : pr[u]);
                 }
@@ -918,7 +941,7 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                     if (ballot(to[u] > 32)) {
                         const bool over = to[u] > 32 && !no;
                         if (add_slab(global(u, 31), over, pr[u], mix32(b0 + row_of(u))))
-                            out[u] = to[u] - 32;
+                            out[u] = new_to(u);
                     }
                 }
                 // the stores have reached memory before the locks open
@@ -930,14 +953,6 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                     if (want[u] == kEmptyPair && fresh[u] > 1 && to[u] == e[u])
                         __hip_atomic_store(gmem(global(u, to[u])), pr[u], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
-                    if (ballot(out[u] >= 4u)) {
-                        // a repeated key's other inserts: replaced, or the one that was new
-                        const uint32_t f = (uint32_t)__shfl((int)(out[u] | (want[u] == kEmptyPair ? 8u : 0u)),
-                                                            (int)rep[u], 64);
-                        if (out[u] >= 4u)
-                            out[u] = (f & 7u) == kLater ? kLater
-                                     : (f & 8u) && out[u] == 5u ? 1u : 2u;
-                    }
                     if (row_of(u) < nb)
                         res[row_of(u) * 32 + slot] = (uint8_t)out[u];
                 }
@@ -950,8 +965,13 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
             const uint32_t q = i + lane;
             uint32_t code = 0, pos = 0;
             if (q < count) {
-                pos = R.shift[owner[q]] + q0 + q;
+                const uint32_t o = owner[q];
+                pos = R.shift[o & kTileOf] + q0 + q;
                 code = line[q] & kNoLine ? line[q] & 3u : res[line[q]];
+                if (code == kNewOther)
+                    code = o & kNewTo ? 1u : 2u;
+                else if ((o & kRepeat) && code != kLater)
+                    code = 2;
                 if (code != kLater)
                     A.flag[pos] = (uint8_t)code;
             }
