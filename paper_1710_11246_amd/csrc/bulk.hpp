@@ -657,7 +657,10 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 //                fill in order: an insert of another kernel that has read the slab meets the lock
 //                at the first empty slot and reads the slab again, so no key can enter twice.
 //                (One new pair is swapped in as it is.)
-//   new values   each replaced slot is swapped from what it holds now, key unchanged.
+//   new values   each replaced slot is swapped from what it holds now, key unchanged. Only pairs
+//                whose bit of the bucket's 512 an insert has set (see below) are compared with the
+//                inserts: comparing every pair took 2^22 inserts on 19 pairs a bucket, 6 more
+//                each, 472 us where this takes 319 (plain 332).
 //
 // What a list of one slab has no room for goes to a new slab, whole before it is linked (left to
 // the plain kernel, where a wavefront adds one slab a round, the 2500 such pairs of 2^22 took
@@ -696,7 +699,7 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
     constexpr uint32_t kRepeat = 0x8000u, kNewTo = 0x4000u, kTileOf = 0x3FFFu;
     uint64_t *pairs = sm8; // the buckets' lines
     uint32_t *sig = reinterpret_cast<uint32_t *>(pairs + ((A.span * kRowWords + 1) & ~1u));
-    uint8_t *res = reinterpret_cast<uint8_t *>(sig); // 32 results per line, once the bits are done
+    uint8_t *res = reinterpret_cast<uint8_t *>(pairs); // a line's results, once its pairs are read
     uint32_t *cnt = sig + A.span * kSigWords;
     uint32_t *again = cnt + A.span;  // bit i: the line's insert i found its bit set
     uint32_t *shared = again + A.span; // bit i: it keeps its place for others of its key too
@@ -894,18 +897,20 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                     to[u] = 32;
                     out[u] = has ? kLater : 0u;
                     want[u] = kEmptyPair;
-                    // keys that are there: the slots' live pairs, one after another
-                    const uint64_t live = ballot(in && slot < 31 && (uint32_t)x != kEmpty);
-                    if (ballot(has)) {
-                        for (uint32_t m = (uint32_t)live | (uint32_t)(live >> 32); m; m &= m - 1) {
-                            const uint32_t s = (uint32_t)__builtin_ctz(m);
-                            const uint32_t ka = rl((uint32_t)x, s), kb = rl((uint32_t)x, s + 32);
-                            const uint32_t va = rl((uint32_t)(x >> 32), s);
-                            const uint32_t vb = rl((uint32_t)(x >> 32), s + 32);
-                            if (has && key == (half ? kb : ka)) {
-                                to[u] = s;
-                                want[u] = ((uint64_t)(half ? vb : va) << 32) | key;
-                            }
+                    // keys that are there: the live pairs whose bit an insert has set, one after
+                    // another
+                    const uint32_t h = ((uint32_t)x * 0x9E3779B1u) >> 23;
+                    const uint32_t bits = in ? sig[row_of(u) * kSigWords + (h >> 5)] : 0u;
+                    const uint64_t live = ballot(slot < 31 && (uint32_t)x != kEmpty &&
+                                                 ((bits >> (h & 31u)) & 1u));
+                    for (uint32_t m = (uint32_t)live | (uint32_t)(live >> 32); m; m &= m - 1) {
+                        const uint32_t s = (uint32_t)__builtin_ctz(m);
+                        const uint32_t ka = rl((uint32_t)x, s), kb = rl((uint32_t)x, s + 32);
+                        const uint32_t va = rl((uint32_t)(x >> 32), s);
+                        const uint32_t vb = rl((uint32_t)(x >> 32), s + 32);
+                        if (has && key == (half ? kb : ka)) {
+                            to[u] = s;
+                            want[u] = ((uint64_t)(half ? vb : va) << 32) | key;
                         }
                     }
                     const uint32_t nm = half_of(ballot(has && to[u] == 32));
@@ -954,7 +959,7 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
                         __hip_atomic_store(gmem(global(u, to[u])), pr[u], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                     if (row_of(u) < nb)
-                        res[row_of(u) * 32 + slot] = (uint8_t)out[u];
+                        res[row_of(u) * (kRowWords * 8) + slot] = (uint8_t)out[u];
                 }
             }
         }
@@ -967,7 +972,8 @@ __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
             if (q < count) {
                 const uint32_t o = owner[q];
                 pos = R.shift[o & kTileOf] + q0 + q;
-                code = line[q] & kNoLine ? line[q] & 3u : res[line[q]];
+                const uint32_t l = line[q];
+                code = l & kNoLine ? l & 3u : res[(l >> 5) * (kRowWords * 8) + (l & 31u)];
                 if (code == kNewOther)
                     code = o & kNewTo ? 1u : 2u;
                 else if ((o & kRepeat) && code != kLater)
