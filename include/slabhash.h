@@ -252,9 +252,12 @@ sh_status_t sh_search(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_
    writes a slab, other inserts into that slab read it again until it is done.
    sh_bulk_bytes gives the workspace (256-byte aligned) that a call of n operations of `kind`
    (SH_OP_SEARCH or SH_OP_INSERT) on `stream` needs now, or 0 where the plain form serves it:
-   small batches, fewer than six operations per bucket, inserts that the base slabs would have no
-   room for, inserts into tables with flags and into tables of a multi-table object, tables with a
-   launch shape set by sh_set_launch, and streams that are being captured. The calls themselves
+   small batches (searches below 2^21, or below 3 * 2^20 of fewer than 2^15 buckets; inserts below
+   2^17), fewer than six operations per bucket, fewer than 1024 buckets and more than about 6.7
+   million (their slabs do not fit the compute units' LDS), inserts beyond 26 per bucket since the
+   last reset (this call and the calls before it, and the operations of mixed batches), inserts
+   into tables with flags and into tables of a multi-table object, tables with a launch shape set
+   by sh_set_launch, and streams that are being captured. The calls themselves
    take the plain form where there is no bulk form or the workspace is missing (NULL) or too
    small. The workspace belongs to one call: its contents need not be set before and mean nothing
    after, and calls that may overlap need one each. It is at most 1.1 GB: longer batches are taken

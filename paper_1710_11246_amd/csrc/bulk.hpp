@@ -23,35 +23,16 @@
 // a searches' merge 12: 4.8), by the ends of their tiles' phases at 2^22. Probe and insert are
 // bound by the chain of waits of a part (run starts, operations, slabs, and the swap and the stores
 // of an insert), which other parts on the same compute unit cover: three of 8 wavefronts at 2^22
-// operations, none at 2^26, where the tiles cannot count more parts and a part's slabs fill the
-// LDS. (Slabs left out of LDS, with only their tags there and a found pair read from L2: more parts
+// operations, none at 2^26, where a part of 16 wavefronts and its slabs fill the LDS (parts that
+// leave room for a second make the runs too short: 256 slabs instead of 340 took 2^26 searches
+// 1.68 ms instead of 1.53). (Slabs left out of LDS, with only their tags there and a found pair read from L2: more parts
 // per compute unit, but 2^22 searches 64 -> 73 us and 2^26 1533 -> 1762 us.)
 //
 // A run of a tile is a few operations (tile / parts), less than a cache line. Workgroups b,
 // b + 8, b + 16, ... share an XCD, so they take consecutive parts: the lines their runs share
 // then meet in that XCD's L2.
 
-constexpr int kSplitThreads = 1024;
-constexpr uint32_t kMaxParts = 15872;     // a tile's part counters fit in LDS beside its keys
-constexpr uint32_t kMaxTiles = 2048;      // run starts of one part, in LDS
-constexpr uint32_t kMaxSpan = 1000;       // buckets of a part (insert_kernel's `line`)
-constexpr uint32_t kRowWords = 33;        // a slab's row in LDS: 32 words and one of padding, so
-                                          // that one slot of many rows spreads over the banks
-
-struct Bulk {
-    uint32_t span, span_magic;   // buckets per part
-    uint32_t parts, tiles, tile; // tile: operations per tile
-    uint32_t row;                // 32-bit words of one tile's row of part starts
-    uint32_t queue;              // operations a probe workgroup takes of its part at a time
-    uint32_t hot;                // a longer run of one part in one tile repeats keys
-    uint16_t *starts;            // tiles rows of parts + 1 starts
-    uint32_t *key;               // operations in tile order; a search's results afterwards
-    uint32_t *val;               // inserts: their values
-    uint32_t *later;             // inserts left to the plain kernel: their positions
-    uint32_t *later_count;
-    uint16_t *place;             // place of each operation of the batch in its tile
-    uint8_t *flag;               // per operation, in tile order
-};
+#include "bulk_plan.hpp"
 
 // Inclusive sum over the wavefront's lanes: four shifts within rows of 16 lanes, then the sums of
 // the rows before (lane 15 of rows 0 and 2 to rows 1 and 3, lane 31 to rows 2 and 3).
@@ -91,9 +72,6 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t *tmp, uint32
     *total = sum;
     return before + incl - x;
 }
-
-// 32-bit words of one tile's part starts: two 16-bit ones each, and the end of the last.
-__host__ __device__ inline uint32_t split_row_words(uint32_t parts) { return parts / 2 + 1; }
 
 // Popular keys repeat within a tile, and would all fall to one part's workgroup. Where a tile's
 // run of one part is longer than distinct keys make it, the run's keys are entered in a small
@@ -683,9 +661,6 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 // where this takes 21.1 with every key twice, 2^18 in 40,960 buckets; 92 us and 86 more in the
 // plain kernel where this takes 71 and 9 with Zipf(0.8) keys, 2^18 in 21,845; and 71.8 us where this
 // takes 73.8 with distinct keys, 2^22 in 217,000.)
-constexpr uint32_t kSigWords = 16;
-constexpr uint32_t kInsRowBytes = kRowWords * 8 + kSigWords * 4 + 12; // LDS per bucket
-
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
 {

@@ -20,6 +20,7 @@
 // decisions and the resulting swaps are committed together (see ops_kernel).
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
@@ -2150,109 +2151,19 @@ sh_status_t launch_ops(sh_table *t, const uint8_t *ops, const uint32_t *keys,
     return check_launch();
 }
 
-// The bulk form's plan for one call: how a batch of n operations on table t is cut into tiles
-// and parts, and where its arrays lie in the workspace.
-struct BulkPlan {
-    uint32_t rows;  // operations per thread of a split workgroup (its tile / 1024)
-    uint32_t waves; // wavefronts of a part's workgroup
-    uint64_t chunk; // operations per pass over the kernels
-    Bulk a;
-    size_t starts, key, val, place, flag, later, total; // byte offsets
-    size_t split_lds, part_lds, merge_lds;
-};
-
-constexpr size_t kLdsBytes = 160 * 1024;
-// Where the bulk form begins, both forms measured on one box (us, plain / bulk):
-//   searches   2^21 at 38, 9.6 and 4.8 per bucket: 61 / 45, 78 / 54, 80 / 65; of popular keys
-//              (Zipf 1.1), which the plain form finds in the caches: 47 / 48, 56 / 59, 59 / 72;
-//              2^20: 33 / 28, and 27 / 33 of popular keys. So 2^21, and six per bucket.
-//   inserts    after a reset, at 19 and 6.4 per bucket: 2^18 57 / 37 and 35 / 35, 2^17 57 / 34
-//              and 28 / 24, 2^16 38 / 32 and 20 / 22, where four launches instead of one cost a
-//              program of small calls more on the host. So 2^17, and six per bucket.
-constexpr uint64_t kBulkSearches = 1u << 21, kBulkInserts = 1u << 17; // the smallest batches
-constexpr uint32_t kBulkCached = 1u << 15;  // base slabs that the L2s hold: 2^21 searches of them
-constexpr uint64_t kBulkCachedSearches = 3u << 20; // take 42 / 46, 2^22 85 / 65
-constexpr uint32_t kBulkPerBucket = 6;      // operations per bucket, at least
-constexpr uint32_t kBulkBuckets = 1u << 10; // a part has at least one, and parts fill the chip
-constexpr uint32_t kBulkFill = 26;          // slots taken per base slab after an insert call, at most
-
-// Whether the call takes the bulk form, and how. A part of about 2048 operations keeps a
-// workgroup of 8 wavefronts busy while three of them share a compute unit's LDS (2^22 searches of
-// 2^22 keys: 79, 62, 64 and 71 us with 1024, 2048, 2560 and 4096 parts); batches with more such
-// parts than a tile can count take larger ones, 16 wavefronts each (2^26 searches: 1.54 ms
-// against 1.92 ms with 8). Tiles grow with the batch: a tile per compute unit at least, and runs
-// of several operations per part.
-bool bulk_plan(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
+// The plan of a call's bulk form (bulk_plan.hpp), if it has one.
+bool bulk_form(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
 {
     const bool ins = kind == kInsert;
-    const uint32_t B = t->v.B;
-    const bool ko = (t->v.mode & SH_TABLE_KEYS_ONLY) != 0;
     if ((kind != kSearch && kind != kInsert) || (ins && (t->v.mode || t->embedded)) || t->flags ||
         t->waves_per_cu || t->ops_per_wave)
         return false;
-    P->chunk = n < (1ull << 26) ? n : (1ull << 26);
-    const uint64_t m = P->chunk;
-    if (m < (ins ? kBulkInserts : B < kBulkCached ? kBulkCachedSearches : kBulkSearches) || m / kBulkPerBucket < B || B < kBulkBuckets)
+    const BulkCall c = {n, t->v.B, (uint32_t)t->num_cu, ins,
+                        (t->v.mode & SH_TABLE_KEYS_ONLY) != 0,
+                        __atomic_load_n(&t->taken, __ATOMIC_RELAXED)};
+    if (!bulk_plan(c, P))
         return false;
-    // inserts that the base slabs have no room for are made the plain way, after the others:
-    // nothing is gained where they are many
-    if (ins && __atomic_load_n(&t->taken, __ATOMIC_RELAXED) + n > (uint64_t)B * kBulkFill)
-        return false;
-    P->rows = m <= (3u << 19) ? 4 : m <= (3u << 20) ? 8 : m <= (1u << 23) ? 16 : 32;
-    Bulk &A = P->a;
-    A.tile = P->rows * kSplitThreads;
-    A.tiles = (uint32_t)((m + A.tile - 1) / A.tile);
-    P->waves = 8;
-    uint64_t parts = (m + 2047) / 2048;
-    if (parts < B / 160)
-        parts = B / 160; // few operations per bucket: the slabs bound the part
-    if (parts > kMaxParts) {
-        P->waves = 16;
-        parts = (m + 6553) / 6554;
-        if (parts < B / 400)
-            parts = B / 400;
-    }
-    const uint64_t cus = (uint64_t)t->num_cu;
-    parts = (parts + cus - 1) / cus * cus;
-    if (parts > kMaxParts)
-        return false;
-    const uint32_t span = (uint32_t)((B + parts - 1) / parts);
-    A.span = span;
-    A.span_magic = magic_for(span);
-    A.parts = (B + span - 1) / span;
-    if (A.parts > kMaxParts || A.tiles > kMaxTiles || span > kMaxSpan)
-        return false;
-    A.row = split_row_words(A.parts);
-    // a part's share varies as a sum of independent operations does
-    const double avg = (double)m / A.parts;
-    A.queue = (uint32_t)(avg + 6 * sqrt(avg) + 64) & ~3u;
-    if (A.queue > 32 * P->waves * 64)
-        A.queue = 32 * P->waves * 64;
-    // more of one part in a tile than distinct keys make by chance
-    const double run = (double)A.tile / A.parts;
-    A.hot = ins ? 0xFFFFu : (uint32_t)(run + 5 * sqrt(run)) + 4;
-    P->split_lds = ((size_t)A.tile + A.row + kSplitThreads / 64 + 1) * 4;
-    const size_t runs = 8 * (size_t)A.tiles + 4 + 4 * P->waves;
-    P->part_lds = ins ? (size_t)span * kInsRowBytes + 8 + runs + 4 * (size_t)A.queue
-                      : (size_t)span * (kRowWords * 8 + (ko ? 64 : 32)) + 8 + runs + 4 +
-                            6 * (size_t)A.queue;
-    P->merge_lds = (size_t)A.tile * (ins ? 1 : 5);
-    if (P->split_lds > kLdsBytes || P->part_lds > kLdsBytes || P->merge_lds > kLdsBytes)
-        return false;
-    const size_t slots = (size_t)A.tiles * A.tile;
-    size_t off = 256;
-    auto take = [&off](size_t bytes) {
-        const size_t at = off;
-        off = round256(off + bytes);
-        return at;
-    };
-    P->starts = take((size_t)A.tiles * A.row * 4);
-    P->key = take(slots * 4);
-    P->place = take(slots * 2);
-    P->flag = take(slots);
-    P->val = ins ? take(slots * 4) : 0;
-    P->later = ins ? take(slots * 4) : 0;
-    P->total = off;
+    P->a.span_magic = magic_for(P->a.span);
     return true;
 }
 
@@ -2779,7 +2690,7 @@ size_t sh_bulk_bytes(const sh_table_t *t, int kind, uint64_t n, void *stream)
 {
     BulkPlan P;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (!t || n == 0 || n >= (1ull << 32) || !bulk_plan(t, kind, n, &P))
+    if (!t || n == 0 || n >= (1ull << 32) || !bulk_form(t, kind, n, &P))
         return 0;
     if (stream && hipStreamIsCapturing(S(stream), &st) != hipSuccess) {
         (void)hipGetLastError(); // left for the call itself to find
@@ -2795,7 +2706,7 @@ sh_status_t sh_search_bulk(sh_table_t *t, const uint32_t *d_keys, uint64_t n, ui
     if (reinterpret_cast<uintptr_t>(d_work) & 255u)
         return SH_EINVAL;
     if (!t || !d_work || n == 0 || n >= (1ull << 32) || !d_keys || !d_vals_out ||
-        !bulk_plan(t, kSearch, n, &P) || work_bytes < P.total)
+        !bulk_form(t, kSearch, n, &P) || work_bytes < P.total)
         return sh_search(t, d_keys, n, d_vals_out, d_found, stream);
     return launch_bulk(t, P, d_keys, nullptr, n, d_vals_out, d_found, static_cast<char *>(d_work),
                        stream);
@@ -2809,7 +2720,7 @@ sh_status_t sh_insert_bulk(sh_table_t *t, const uint32_t *d_keys, const uint32_t
     if (reinterpret_cast<uintptr_t>(d_work) & 255u)
         return SH_EINVAL;
     if (!t || !d_work || n == 0 || n >= (1ull << 32) || !d_keys || !d_vals ||
-        !bulk_plan(t, kInsert, n, &P) || work_bytes < P.total)
+        !bulk_form(t, kInsert, n, &P) || work_bytes < P.total)
         return sh_insert(t, d_keys, d_vals, n, d_status, stream);
     return launch_bulk(t, P, d_keys, d_vals, n, nullptr, d_status, static_cast<char *>(d_work),
                        stream);
