@@ -421,6 +421,7 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
     uint32_t *sh = tmp + NW; // unanswered searches
     uint32_t *queue = sh + 1;
     uint16_t *owner = reinterpret_cast<uint16_t *>(queue + A.queue); // bit 15: found
+    uint8_t *open_row = reinterpret_cast<uint8_t *>(owner + A.queue); // its list is read on
     const uint32_t tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
     const uint32_t half = lane >> 5, slot = lane & 31;
     const uint32_t limit = T.total_blocks * SH_BLOCK_SLABS; // no list has more pool slabs
@@ -459,6 +460,8 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
         }
     };
     fetch_rows(wv * 2); // in flight while the runs are read and summed
+    for (uint32_t r = tid; r < A.span; r += kThreads)
+        open_row[r] = 0;
     const uint32_t total = load_runs<NW>(A, part, R, tmp, owner);
     put_rows(wv * 2);
     bool fresh = true, have = true; // rows to be read; the first of them already there
@@ -528,6 +531,7 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
                     undone &= ~bit;
                 } else {
                     undone |= bit;
+                    open_row[r] = 1;
                 }
             }
             uint32_t mine = (uint32_t)__popcll(undone);
@@ -592,23 +596,27 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
             if (tid == 0)
                 sh[0] = 0;
             __syncthreads();
-            // the next slab of every list replaces its row; the searches of a list without one
-            // have all ended
+            // the next slab of every list with an open search replaces its row (a list without a next
+            // slab has none)
             fresh = true;
             for (uint32_t r0 = wv * 2; r0 < nb; r0 += NW * 2 * kRowLoads) {
                 uint32_t has = 0;
 #pragma unroll
                 for (int u = 0; u < kRowLoads; ++u) {
                     const uint32_t r = r0 + u * NW * 2 + half;
-                    const uint32_t nx = r < nb ? (uint32_t)(rows[r * kRowWords + 31] >> 32) : kEmpty;
+                    const uint32_t nx = r < nb && open_row[r]
+                                            ? (uint32_t)(rows[r * kRowWords + 31] >> 32)
+                                            : kEmpty;
                     has |= nx != kEmpty ? 1u << u : 0u;
                     w[u] = nx != kEmpty && pool_in_range(T, nx) ? *gmem(pool_slab(T, nx) + slot)
                                                                 : ~0ull;
                 }
 #pragma unroll
                 for (int u = 0; u < kRowLoads; ++u)
-                    if ((has >> u) & 1u)
+                    if ((has >> u) & 1u) {
                         put_row(r0 + u * NW * 2 + half, w[u]);
+                        open_row[r0 + u * NW * 2 + half] = 0;
+                    }
             }
             __syncthreads();
         }

@@ -9,9 +9,9 @@ constexpr uint32_t kMaxSpan = 1000;       // buckets of a part (insert_kernel's 
 constexpr uint32_t kRowWords = 33;        // a slab's row in LDS: 32 words and one of padding, so
                                           // that one slot of many rows spreads over the banks
 constexpr uint32_t kSigWords = 16;        // an insert's bucket: 512 bits
-// LDS per bucket of a part. Searches: the row and its tags; inserts: the line, the bits and three
-// words.
-constexpr uint32_t kPairRowBytes = kRowWords * 8 + 32, kKeyRowBytes = kRowWords * 8 + 64;
+// LDS per bucket of a part. Searches: the row, its tags and a byte; inserts: the line, the bits and
+// three words.
+constexpr uint32_t kPairRowBytes = kRowWords * 8 + 32 + 1, kKeyRowBytes = kRowWords * 8 + 64 + 1;
 constexpr uint32_t kInsRowBytes = kRowWords * 8 + kSigWords * 4 + 12;
 constexpr size_t kLdsBytes = 160 * 1024;
 

@@ -68,7 +68,8 @@ def check(p, n, buckets, kind):
     assert p["tile"] <= 1 << 15 and 2 * p["row"] > p["parts"]
     assert 64 <= p["queue"] <= 32 * 64 * p["waves"] and p["queue"] % 4 == 0
     # what the kernels lay out in LDS, and in the workspace
-    row = {"search": 33 * 8 + 32, "search of keys": 33 * 8 + 64, "insert": 33 * 8 + 64 + 12}[kind]
+    row = {"search": 33 * 8 + 32 + 1, "search of keys": 33 * 8 + 64 + 1,
+           "insert": 33 * 8 + 64 + 12}[kind]
     runs = 8 * p["tiles"] + 4 + 4 * p["waves"]
     need = p["span"] * row + 8 + runs + (4 * p["queue"] if kind == "insert" else 4 + 6 * p["queue"])
     assert p["part_lds"] >= need
