@@ -112,8 +112,8 @@ def op_bytes(kind: str, n: int, v_hit: float, v_miss: float, new_slabs: int = 0,
 def bulk_forms(handle, n: int) -> dict:
     """Which calls of n ops take the bulk form on this table, which must be empty."""
     from paper_1710_11246_amd import slabhash as S
-    search = S.sh_bulk_bytes(handle, S.SH_OP_SEARCH, n) > 0
-    return {"build": S.sh_bulk_bytes(handle, S.SH_OP_INSERT, n) > 0, "search_hit": search,
+    search = S.sh_bulk_choice(handle, S.SH_OP_SEARCH, n) > 0
+    return {"build": S.sh_bulk_choice(handle, S.SH_OP_INSERT, n) > 0, "search_hit": search,
             "search_miss": search}
 
 

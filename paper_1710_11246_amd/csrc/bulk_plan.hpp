@@ -149,3 +149,38 @@ inline bool bulk_plan(const BulkCall &c, BulkPlan *P)
     P->total = off;
     return true;
 }
+
+// Whether the bulk form is the faster one for the call, whatever its keys: distinct, repeated or
+// popular, present or absent. Each line lies where the slowest distribution measured is level with
+// the plain form (us, plain / bulk; Zipf(0.8) and Zipf(1.1) ranks; "half" with half of them absent):
+//
+//   searches   the plain form finds popular keys in the caches, and three launches instead of one
+//              cost 10 us: 2.5 * 2^20 at 10 per bucket uniform 101 / 74 but Zipf(1.1) 74 / 80, half
+//              76 / 86; at 40, 82 / 54, 63 / 62, 65 / 73. 3.5 * 2^20 at 10: 145 / 85, 100 / 90,
+//              101 / 94. At 2^26 at 10: 3258 / 1885, 1521 / 1517. So 3.5 * 2^20, ten per bucket.
+//              Longer lists than one slab are read level by level for all of a part: with 40 pairs
+//              per bucket 2^22 at 10 197 / 148 but Zipf(0.8) 156 / 175, at 16 189 / 115, 152 / 145;
+//              with 150, Zipf(1.1) at 16 190 / 222 (uniform 462 / 254), with 400 at 64 370 / 383.
+//              So 16 per bucket, and 64, of tables that may hold that much.
+//   inserts    into an empty table, every key once / every key twice: 2^17 at 6.1 per bucket 26 / 26
+//              and 22 / 27, at 10 35 / 24 and 26 / 25; 2^18 at 7 33 / 33 and 29 / 35, at 10 37 / 27
+//              and 31 / 29; 3 * 2^17 at 6.1 39 / 33 and 36 / 34. Popular keys gain most.
+//              Beside pairs that the table holds, fresh keys / keys that are all present: 2^18 at
+//              12 on 12 held 47 / 30 and 23 / 37 (a plain insert finds such a key and swaps once);
+//              2^20 92 / 55 and 68 / 69; 2^22 at 8 on 12 266 / 215 and 251 / 257, at 12 289 / 182
+//              and 243 / 209. So 2^20 and 12 per bucket there.
+//
+// counted: no operations but those in since_reset have reached the table.
+inline bool bulk_pays(const BulkCall &c, bool counted)
+{
+    const uint64_t m = c.n < (1ull << 26) ? c.n : (1ull << 26), B = c.buckets;
+    const uint64_t slab = c.keys_only ? 62 : 31; // entries
+    if (!c.insert) {
+        const uint64_t held = c.since_reset;
+        const uint64_t per = !counted || held > 2 * slab * B ? 64 : held > slab * B * 2 / 3 ? 16 : 10;
+        return c.n >= (7u << 19) && m / per >= B;
+    }
+    if (c.since_reset == 0)
+        return c.n >= (1u << 17) && m / (c.n < (3u << 17) ? 10 : 6) >= B;
+    return c.n >= (1u << 20) && m / 12 >= B;
+}

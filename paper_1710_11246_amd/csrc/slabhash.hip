@@ -2151,8 +2151,8 @@ sh_status_t launch_ops(sh_table *t, const uint8_t *ops, const uint32_t *keys,
     return check_launch();
 }
 
-// The plan of a call's bulk form (bulk_plan.hpp), if it has one.
-bool bulk_form(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
+// The plan of a call's bulk form (bulk_plan.hpp), if it has one; `pays`: and if it is the faster one.
+bool bulk_form(const sh_table *t, int kind, uint64_t n, BulkPlan *P, bool pays = false)
 {
     const bool ins = kind == kInsert;
     if ((kind != kSearch && kind != kInsert) || (ins && (t->v.mode || t->embedded)) || t->flags ||
@@ -2161,7 +2161,7 @@ bool bulk_form(const sh_table *t, int kind, uint64_t n, BulkPlan *P)
     const BulkCall c = {n, t->v.B, (uint32_t)t->num_cu, ins,
                         (t->v.mode & SH_TABLE_KEYS_ONLY) != 0,
                         __atomic_load_n(&t->taken, __ATOMIC_RELAXED)};
-    if (!bulk_plan(c, P))
+    if ((pays && !bulk_pays(c, !t->embedded)) || !bulk_plan(c, P))
         return false;
     P->a.span_magic = magic_for(P->a.span);
     return true;
@@ -2233,6 +2233,20 @@ sh_status_t launch_bulk(sh_table *t, const BulkPlan &P, const uint32_t *keys, co
             return SH_EHIP;
     }
     return SH_OK;
+}
+
+// The workspace of a call's bulk form on `stream`, or 0.
+size_t bulk_bytes(const sh_table *t, int kind, uint64_t n, void *stream, bool pays)
+{
+    BulkPlan P;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!t || n == 0 || n >= (1ull << 32) || !bulk_form(t, kind, n, &P, pays))
+        return 0;
+    if (stream && hipStreamIsCapturing(S(stream), &st) != hipSuccess) {
+        (void)hipGetLastError(); // left for the call itself to find
+        return 0;
+    }
+    return st == hipStreamCaptureStatusNone ? P.total : 0;
 }
 
 sh_status_t walk(sh_table *t, uint32_t *dbkt, uint32_t *dkey, uint32_t *dval, uint64_t cap,
@@ -2688,15 +2702,12 @@ sh_status_t sh_search(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_
 
 size_t sh_bulk_bytes(const sh_table_t *t, int kind, uint64_t n, void *stream)
 {
-    BulkPlan P;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (!t || n == 0 || n >= (1ull << 32) || !bulk_form(t, kind, n, &P))
-        return 0;
-    if (stream && hipStreamIsCapturing(S(stream), &st) != hipSuccess) {
-        (void)hipGetLastError(); // left for the call itself to find
-        return 0;
-    }
-    return st == hipStreamCaptureStatusNone ? P.total : 0;
+    return bulk_bytes(t, kind, n, stream, false);
+}
+
+size_t sh_bulk_choice(const sh_table_t *t, int kind, uint64_t n, void *stream)
+{
+    return bulk_bytes(t, kind, n, stream, true);
 }
 
 sh_status_t sh_search_bulk(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_t *d_vals_out,

@@ -102,6 +102,7 @@ _SIGS = {
     "sh_delete": ([_P, _P, _U64, _P, _P], ctypes.c_int),
     "sh_search": ([_P, _P, _U64, _P, _P, _P], ctypes.c_int),
     "sh_bulk_bytes": ([_P, ctypes.c_int, _U64, _P], _SZ),
+    "sh_bulk_choice": ([_P, ctypes.c_int, _U64, _P], _SZ),
     "sh_search_bulk": ([_P, _P, _U64, _P, _P, _P, _SZ, _P], ctypes.c_int),
     "sh_insert_bulk": ([_P, _P, _P, _U64, _P, _P, _SZ, _P], ctypes.c_int),
     "sh_mixed": ([_P, _P, _P, _P, _U64, _P, _P, _P], ctypes.c_int),
@@ -197,12 +198,16 @@ def _outside_captures():
         exchange(ctypes.byref(mode))
 
 
-#: No batch below these takes the bulk form (the library's own lines lie at or above them).
-_BULK_MIN = {SH_OP_SEARCH: 1 << 21, SH_OP_INSERT: 1 << 17}
+#: No batch below these takes the bulk form (sh_bulk_choice's lines).
+_BULK_MIN = {SH_OP_SEARCH: 7 << 19, SH_OP_INSERT: 1 << 17}
 
 
 def sh_bulk_bytes(t, kind: int, n: int, stream=None) -> int:
     return int(lib().sh_bulk_bytes(t, int(kind), int(n), _stream(stream)))
+
+
+def sh_bulk_choice(t, kind: int, n: int, stream=None) -> int:
+    return int(lib().sh_bulk_choice(t, int(kind), int(n), _stream(stream)))
 
 
 def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
@@ -215,7 +220,7 @@ def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     if n < _BULK_MIN[kind]:
         return None
     raw = _stream(stream)
-    nbytes = lib().sh_bulk_bytes(t, kind, n, raw)
+    nbytes = lib().sh_bulk_choice(t, kind, n, raw)
     if nbytes == 0:
         return None
     if stream is None or raw == _current_stream():

@@ -11,12 +11,12 @@ class Library:
     def __init__(self):
         self.asked = []
 
-    def sh_bulk_bytes(self, t, kind, n, stream):
+    def sh_bulk_choice(self, t, kind, n, stream):
         self.asked.append((kind, n, stream))
         return 0
 
 
-@pytest.mark.parametrize("kind,n", [(S.SH_OP_SEARCH, 1 << 21), (S.SH_OP_INSERT, 1 << 17)])
+@pytest.mark.parametrize("kind,n", [(S.SH_OP_SEARCH, 7 << 19), (S.SH_OP_INSERT, 1 << 17)])
 def test_a_call_without_a_bulk_form_builds_no_stream_object(monkeypatch, kind, n):
     """Large enough to ask, refused by the library: one question, by the stream's number."""
     def no(*a, **k):

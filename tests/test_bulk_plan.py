@@ -32,6 +32,13 @@ extern "C" int plan(uint64_t n, uint32_t buckets, uint32_t num_cu, int insert, i
 """
 FIELDS = ("rows waves chunk span parts tiles tile row queue split_lds part_lds merge_lds "
           "starts key place flag val later total").split()
+PAYS = """
+extern "C" int pays(uint64_t n, uint32_t buckets, int insert, int keys_only, uint64_t since_reset,
+                    int counted)
+{
+    return bulk_pays(BulkCall{n, buckets, 256, insert != 0, keys_only != 0, since_reset}, counted);
+}
+"""
 KINDS = ["search", "search of keys", "insert"]
 TOP = 1 << 26           # operations of a batch that is not taken in pieces
 LARGEST = 6_600_000     # buckets whose slabs fit the compute units' LDS in every kind
@@ -39,13 +46,27 @@ LEAST = {"search": 1 << 21, "search of keys": 1 << 21, "insert": 1 << 17}
 
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def library(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
     src, lib = str(d / "plan.cpp"), str(d / "plan.so")
-    open(src, "w").write(DRIVER)
+    open(src, "w").write(DRIVER + PAYS)
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
                            "-I", CSRC, src, "-o", lib])
-    f = ctypes.CDLL(lib).plan
+    return ctypes.CDLL(lib)
+
+
+@pytest.fixture(scope="module")
+def pays(library):
+    f = library.pays
+    f.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int, ctypes.c_int, ctypes.c_uint64,
+                  ctypes.c_int]
+    return lambda n, buckets, kind, held=0, counted=True: bool(
+        f(n, buckets, kind == "insert", kind == "search of keys", held, counted))
+
+
+@pytest.fixture(scope="module")
+def plan(library):
+    f = library.plan
     f.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_int, ctypes.c_int,
                   ctypes.c_uint64, ctypes.c_void_p]
 
@@ -146,3 +167,48 @@ def test_lines(plan):
     assert plan(26 * 20000, 20000, "insert") and plan(26 * 20000 + 1, 20000, "insert") is None
     assert plan(20 * 20000, 20000, "insert", since_reset=6 * 20000)
     assert plan(20 * 20000, 20000, "insert", since_reset=6 * 20000 + 1) is None
+
+
+@pytest.mark.parametrize("kind", ["search", "search of keys"])
+def test_where_searches_pay(pays, kind):
+    """Per bucket: 10 of lists of one slab, 16 up to two slabs, 64 beyond and where it is unknown."""
+    slab = 62 if kind == "search of keys" else 31
+    n = 7 << 19
+    assert pays(n, 60000, kind) and not pays(n - 1, 60000, kind)
+    for n in (7 << 19, 1 << 23, 1 << 26, 1 << 28):
+        m = min(n, TOP)
+        for per_slab, per in ((0, 10), (2 / 3 - .01, 10), (2 / 3 + .01, 16), (1.99, 16), (2.01, 64),
+                              (50, 64)):
+            b = m // per
+            assert pays(n, b, kind, int(per_slab * slab * b))
+            assert not pays(n, b + 1, kind, int(per_slab * slab * (b + 1)))
+        assert pays(n, m // 64, kind, 0, False) and not pays(n, m // 64 + 1, kind, 0, False)
+
+
+def test_where_inserts_pay(pays):
+    """An empty table from 2^17 at ten per bucket and from 3 * 2^17 at six; any other from 2^20 at
+    twelve."""
+    for n, per in ((1 << 17, 10), ((3 << 17) - 1, 10), (3 << 17, 6), (1 << 26, 6)):
+        assert pays(n, n // per, "insert") and not pays(n, n // per + 1, "insert")
+    assert not pays((1 << 17) - 1, 2000, "insert")
+    for held in (1, 100000):
+        assert pays(1 << 20, (1 << 20) // 12, "insert", held)
+        assert not pays(1 << 20, (1 << 20) // 12 + 1, "insert", held)
+        assert not pays((1 << 20) - 1, 20000, "insert", held)
+
+
+def test_what_pays_has_a_plan(plan, pays):
+    """From 1024 buckets up to those whose slabs fit, and within the base slabs' room."""
+    rng = random.Random(9)
+    found = 0
+    for _ in range(20000):
+        kind = rng.choice(KINDS)
+        n = int(2 ** rng.uniform(17, 28))
+        b = int(n / 2 ** rng.uniform(1, 8))
+        held = rng.choice([0, 0, int(b * rng.uniform(0, 30))])
+        if not 1024 <= b <= LARGEST or kind == "insert" and n + held > 26 * b:
+            continue
+        if pays(n, b, kind, held):
+            found += 1
+            assert plan(n, b, kind, since_reset=held)
+    assert found > 500

@@ -9,7 +9,7 @@ import torch
 from paper_1710_11246_amd import slabhash as S
 
 pytestmark = pytest.mark.gpu
-N = 3 << 20
+N = 1 << 22
 
 
 def say(*a):
@@ -34,6 +34,7 @@ def test_large_calls_beside_a_capture(who):
     v, f = torch.zeros_like(k), torch.zeros(N, dtype=torch.uint8, device="cuda")
     few = torch.zeros(1024, dtype=torch.int32, device="cuda")
     captured, call = torch.cuda.Stream(), torch.cuda.Stream()
+    assert S.sh_bulk_choice(t.handle, S.SH_OP_SEARCH, N, call) > 0
     torch.cuda.synchronize()
     torch.cuda.empty_cache()  # the call's workspace has to come from the device
     errors = []
