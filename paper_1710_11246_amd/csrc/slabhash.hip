@@ -1905,7 +1905,12 @@ struct sh_table {
     struct sh_multi *owner; // that object, and this table's index in it
     uint32_t index;
     uint64_t super_slabs; // slabs of the super blocks registered beyond super block 0
-    uint64_t taken;       // inserts since the last reset: a bound on the slots in use
+    // Inserts, replacing ones too, and operations of mixed batches since the last reset, as the
+    // host enqueued them: for the choice between the plain and the bulk form alone, which give the
+    // same results. It is neither exact nor a bound of what the table holds: replaced, deleted and
+    // flushed pairs stay in it, a captured call counts once whether its graph is replayed or not,
+    // and calls through a multi-table object are not in it.
+    uint64_t since_reset;
 };
 
 struct sh_multi {
@@ -2145,7 +2150,7 @@ sh_status_t launch_ops(sh_table *t, const uint8_t *ops, const uint32_t *keys,
     const dim3 grid(grid_for(t, n, C, wpc));
     const uint32_t seq = next_seq(&t->seq);
     if constexpr (K == kInsert || K == kMixed)
-        __atomic_fetch_add(&t->taken, n, __ATOMIC_RELAXED);
+        __atomic_fetch_add(&t->since_reset, n, __ATOMIC_RELAXED);
     hipLaunchKernelGGL(fn, grid, dim3(kBlock), 0, S(stream), t->v, ops, keys, vals, n, vout, sout,
                        seq, t->flags);
     return check_launch();
@@ -2160,7 +2165,7 @@ bool bulk_form(const sh_table *t, int kind, uint64_t n, BulkPlan *P, bool pays =
         return false;
     const BulkCall c = {n, t->v.B, (uint32_t)t->num_cu, ins,
                         (t->v.mode & SH_TABLE_KEYS_ONLY) != 0,
-                        __atomic_load_n(&t->taken, __ATOMIC_RELAXED)};
+                        __atomic_load_n(&t->since_reset, __ATOMIC_RELAXED)};
     if ((pays && !bulk_pays(c, !t->embedded)) || !bulk_plan(c, P))
         return false;
     P->a.span_magic = magic_for(P->a.span);
@@ -2209,7 +2214,7 @@ sh_status_t launch_bulk(sh_table *t, const BulkPlan &P, const uint32_t *keys, co
                       : ko ? (wide ? probe_kernel<true, 16> : probe_kernel<true, 8>)
                            : (wide ? probe_kernel<false, 16> : probe_kernel<false, 8>);
     if (ins)
-        __atomic_fetch_add(&t->taken, n, __ATOMIC_RELAXED);
+        __atomic_fetch_add(&t->since_reset, n, __ATOMIC_RELAXED);
     if (!allow_lds(split, P.split_lds) || !allow_lds(merge, P.merge_lds) ||
         !allow_lds(part, P.part_lds))
         return SH_EHIP;
@@ -2436,7 +2441,12 @@ sh_status_t sh_reset(sh_table_t *t, void *stream)
 {
     if (!t)
         return SH_EINVAL;
-    __atomic_store_n(&t->taken, 0, __ATOMIC_RELAXED);
+    // a captured reset has not run: what the table holds stays counted
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (stream && hipStreamIsCapturing(S(stream), &st) != hipSuccess)
+        (void)hipGetLastError(); // left for the launch to find
+    if (st == hipStreamCaptureStatusNone)
+        __atomic_store_n(&t->since_reset, 0, __ATOMIC_RELAXED);
     Layout L;
     layout_of(&t->p, &L);
     const size_t hdr16 = kHeaderBytes / 16;
