@@ -1600,9 +1600,12 @@ __global__ __launch_bounds__(kBlock) void all_kernel(View T, const uint32_t *__r
 // block's sum in work[1 + block], the second adds up those before its own (n / 8192 words, from
 // the caches) and scans its counts; the last block leaves the total in work[0]. Launch latency
 // bounds both: 2^18 counts take 11 us, the library calls for it before (widen, clear, scan,
-// widen, sum) 43 us.
+// widen, sum) 43 us. Beyond kScanDirect blocks, where adding up grows with the square of n, one
+// block turns the sums into those before each in a launch between the two: 2^25 counts 213 us
+// either way, 2^26 424 -> 413, 2^28 1.67 -> 1.52 ms, 2^30 8.48 -> 5.96.
 constexpr int kScanThreads = 1024;
 constexpr uint32_t kScanBlock = kScanThreads * 8;
+constexpr uint32_t kScanDirect = 4096;
 
 __device__ __forceinline__ uint64_t wave_sum64(uint64_t x)
 {
@@ -1626,7 +1629,54 @@ __device__ __forceinline__ uint64_t block_sum64(uint64_t x, uint64_t *tmp)
     return all;
 }
 
-template <bool Write>
+// The sum of x over the block's threads up to this one.
+__device__ __forceinline__ uint64_t block_scan64(uint64_t x, uint64_t *tmp)
+{
+    const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint64_t t = (uint64_t)__shfl_up((unsigned long long)x, d, 64);
+        if (lane >= (uint32_t)d)
+            x += t;
+    }
+    if (lane == 63)
+        tmp[wv] = x;
+    __syncthreads();
+    for (uint32_t w = 0; w < wv; ++w)
+        x += tmp[w];
+    return x;
+}
+
+// One block: work[1 .. blocks] become the sums before them.
+__global__ __launch_bounds__(kScanThreads) void block_sums_kernel(uint64_t *work, uint32_t blocks)
+{
+    __shared__ uint64_t tmp[kScanThreads / 64], total;
+    uint64_t carry = 0;
+    for (uint32_t b0 = 0; b0 < blocks; b0 += kScanBlock) {
+        const uint32_t i0 = b0 + threadIdx.x * 8;
+        uint64_t s[8], mine = 0;
+#pragma unroll
+        for (uint32_t e = 0; e < 8; ++e) {
+            s[e] = i0 + e < blocks ? work[1 + i0 + e] : 0ull;
+            mine += s[e];
+        }
+        const uint64_t incl = carry + block_scan64(mine, tmp);
+        if (threadIdx.x == kScanThreads - 1)
+            total = incl;
+        uint64_t at = incl - mine;
+#pragma unroll
+        for (uint32_t e = 0; e < 8; ++e) {
+            if (i0 + e < blocks)
+                work[1 + i0 + e] = at;
+            at += s[e];
+        }
+        __syncthreads();
+        carry = total;
+    }
+}
+
+// Write: offsets from the counts and the blocks' sums, or (Before) from the sums before each.
+template <bool Write, bool Before>
 __global__ __launch_bounds__(kScanThreads) void offsets_kernel(const uint32_t *__restrict__ counts,
                                                                uint64_t n,
                                                                uint64_t *__restrict__ offsets,
@@ -1657,9 +1707,13 @@ __global__ __launch_bounds__(kScanThreads) void offsets_kernel(const uint32_t *_
             work[1 + blockIdx.x] = sum;
     } else {
         uint64_t before = 0;
-        for (uint32_t b = tid; b < blockIdx.x; b += kScanThreads)
-            before += work[1 + b];
-        before = block_sum64(before, tmp);
+        if constexpr (Before) {
+            before = work[1 + blockIdx.x];
+        } else {
+            for (uint32_t b = tid; b < blockIdx.x; b += kScanThreads)
+                before += work[1 + b];
+            before = block_sum64(before, tmp);
+        }
         uint64_t incl = mine; // over the wavefront's lanes
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
@@ -2593,10 +2647,14 @@ sh_status_t sh_search_all_offsets(const uint32_t *d_counts, uint64_t n, uint64_t
     // (no counts: one block that leaves a total of 0)
     const dim3 grid(n ? (uint32_t)((n + kScanBlock - 1) / kScanBlock) : 1u);
     if (n > kScanBlock)
-        hipLaunchKernelGGL(offsets_kernel<false>, grid, dim3(kScanThreads), 0, S(stream), d_counts,
-                           n, d_offsets, d_work);
-    hipLaunchKernelGGL(offsets_kernel<true>, grid, dim3(kScanThreads), 0, S(stream), d_counts, n,
-                       d_offsets, d_work);
+        hipLaunchKernelGGL((offsets_kernel<false, false>), grid, dim3(kScanThreads), 0, S(stream),
+                           d_counts, n, d_offsets, d_work);
+    const bool direct = grid.x <= kScanDirect;
+    if (!direct)
+        hipLaunchKernelGGL(block_sums_kernel, dim3(1), dim3(kScanThreads), 0, S(stream), d_work,
+                           grid.x);
+    hipLaunchKernelGGL((direct ? offsets_kernel<true, false> : offsets_kernel<true, true>), grid,
+                       dim3(kScanThreads), 0, S(stream), d_counts, n, d_offsets, d_work);
     return check_launch();
 }
 
