@@ -400,7 +400,7 @@ template <bool KO> constexpr uint32_t kTagWords = KO ? 16u : 8u;
 // Searches of one part. LDS: the rows of the part's slabs, their tags, the runs, and a queue of
 // the part's searches: their keys, which the results replace, and the tiles they come from. (A
 // queue in LDS, not in registers: eight searches a thread in registers left three wavefronts per
-// SIMD where this form runs eight, and took 62 us where it takes 37: 2^22 searches, 2^22 keys.)
+// SIMD where this form runs six, and took 62 us where it takes 37: 2^22 searches, 2^22 keys.)
 // Lists longer than one slab are taken level by level: while many searches still run, the next
 // slab of every list that has one replaces its row; a wavefront with few left walks their lists
 // itself, one per half wavefront. A thread keeps the searches it has not answered as bits, search tid + i * threads
@@ -632,11 +632,9 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
     }
 }
 
-// Inserts of one part, on a unique-key pair table (REPLACE). The part's slabs come to LDS as a
-// probe's do, and its inserts are made there first: one that finds its key gives the slot its
-// value (status 2), another takes the first empty slot by a 64-bit swap (status 1), so that the
-// repeated keys of a batch meet in one slot as they would in the table. Then the rows are
-// committed to the table, half a wavefront per slab:
+// Inserts of one part, on a unique-key pair table (REPLACE). They are gathered by bucket in LDS, and
+// half a wavefront per slab commits them to the table: one that finds its key gives the slot its
+// value (status 2), another takes the next empty slot (status 1).
 //
 //   new pairs    the first empty slot is swapped to kLockPair, the pairs of the slots after it
 //                are stored in one piece, and the pair of the locked slot is stored last. Slots
@@ -651,8 +649,12 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 // What a list of one slab has no room for goes to a new slab, whole before it is linked (left to
 // the plain kernel, where a wavefront adds one slab a round, the 2500 such pairs of 2^22 took
 // 17 us). What loses a swap to another kernel's update, and the inserts into longer lists, are
-// listed for the plain kernel, which runs next. A lock is held for the time of two or three memory
-// round trips by a wavefront that waits for nothing else meanwhile.
+// listed for the plain kernel, which runs next. A half wavefront takes four slabs at a time, and
+// their locks open together: after three memory round trips (its own swap, the stores, the opening)
+// where no list grows, and after up to eleven more for each of the four that does (eight bitmap
+// words tried, the new pairs, the link, and if it is lost the clearing). It waits for nothing else
+// meanwhile. (Opening the locks of lists that do not grow first took the kernel 76.4 us instead of
+// 75.1: 2^22 inserts in 217,000 buckets.)
 //
 // One swap a slab instead of one a pair, and stores of whole runs of slots: 2^22 random swaps
 // take 158 us on this memory, swaps of 19 adjacent slots 49 us, stores of them 18 us.
