@@ -40,7 +40,7 @@ B_FOR_UTIL = {0.2: 654181, 0.3: 436670, 0.4: 327431, 0.5: 261962, 0.6: 217316, 0
 
 # Bytes per launch beyond L2 (reads + writes), from rocprofv3 FETCH_SIZE/WRITE_SIZE runs scaled by
 # a 1 GiB device copy; see profiles/slabhash_step_2p22_traffic.md. Valid only for the kernel
-# source they were measured on (sha256 prefix of csrc/slabhash.hip); otherwise reported as null.
+# source they were measured on (source_sha); otherwise reported as null.
 TRAFFIC_SRC_SHA = "f87bfcd2f0d57c57"
 # Per launch, from rocprofv3 TCC_HIT_sum/TCC_MISS_sum and TCC_ATOMIC_sum/TCC_EA0_ATOMIC_sum runs
 # of the same source (profiles/slabhash_step_2p22_l2.md): (L2 hit rate, atomics, atomics that
@@ -56,9 +56,14 @@ TRAFFIC_BYTES = {"build": 1349499276, "search_hit": 1039525491, "search_miss": 1
 
 
 def source_sha() -> str:
+    """sha256 prefix of the library's kernel source: csrc/slabhash.hip and the files it includes."""
+    import glob
     import hashlib
-    path = os.path.join(ROOT, "paper_1710_11246_amd", "csrc", "slabhash.hip")
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+    csrc = os.path.join(ROOT, "paper_1710_11246_amd", "csrc")
+    h = hashlib.sha256()
+    for path in [os.path.join(csrc, "slabhash.hip"), *sorted(glob.glob(os.path.join(csrc, "*.hpp")))]:
+        h.update(open(path, "rb").read())
+    return h.hexdigest()[:16]
 
 
 def log(*a):
