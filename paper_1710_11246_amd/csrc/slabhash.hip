@@ -126,9 +126,6 @@ __device__ __forceinline__ bool inverse_ballot(uint64_t m)
     return __builtin_amdgcn_inverse_ballot_w64(m);
 }
 
-// Lanes holding a slot of a slab: every lane but slot 31 of each half (the next index).
-constexpr uint64_t kSlotLanes = ~((1ull << 31) | (1ull << 63));
-
 // A wave-uniform 64-bit value kept in scalar registers. (The builtin returns int: each half is
 // taken back to uint32_t before widening, or the low half would be sign-extended.)
 __device__ __forceinline__ uint64_t uniform64(uint64_t x)
