@@ -921,10 +921,6 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                     // return; at most the 31 slots of this slab. (With duplicates, empty slots
                     // need not be a suffix, so a lost insert re-reads its slab next round.)
                     for (;;) {
-                        if (Locks && old == kLockPair) {
-                            lost = true; // a bulk insert holds the slab: read it again
-                            break;
-                        }
                         if ((uint32_t)old == key) { // the same key was inserted: replace it
                             expect = old;
                             old = cas64(slab + cslot, expect, desired);
@@ -936,7 +932,11 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                             }
                             break;
                         }
-                        if (++cslot >= 31) {
+                        // A slab that a bulk insert holds ends the walk as a full one does. (An
+                        // exit of its own took 1000 inserts into 66 buckets 18.0 us instead of 17.4
+                        // (16.8 without a lock to look for): every step of the walk has it.)
+                        cslot = Locks && old == kLockPair ? 31u : cslot + 1;
+                        if (cslot >= 31) {
                             lost = true; // slab filled up: the next round follows `next`
                             break;
                         }
