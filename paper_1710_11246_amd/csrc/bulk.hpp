@@ -13,10 +13,10 @@
 // mean of all present and all absent):
 //
 //                     plain   bulk   of it: split   probe / insert   later   merge
-//   2^22 searches       152     69             15               41               9
-//   2^26 searches      2890   1430            200             1070             168
-//   2^22 inserts        239    114             20               72      11       6
-//   2^26 inserts       4340   2070            293             1700      19      57
+//   2^22 searches       149     67             16               42               9
+//   2^26 searches      2890   1440            209             1070             167
+//   2^22 inserts        239    111             21               74      11       5
+//   2^26 inserts       4260   2010            296             1650      19      59
 //
 // The plain form reads 256 bytes at random per operation, and an insert swaps 8. Split and merge
 // are bound by memory at 2^26 (split moves 11 bytes per search and 18 per insert: 3.7 and 4.1 TB/s;
@@ -25,8 +25,8 @@
 // of an insert), which other parts on the same compute unit cover: three of 8 wavefronts at 2^22
 // operations, none at 2^26, where a part of 16 wavefronts and its slabs fill the LDS (parts that
 // leave room for a second make the runs too short: 256 slabs instead of 340 took 2^26 searches
-// 1.68 ms instead of 1.53). (Slabs left out of LDS, with only their tags there and a found pair read from L2: more parts
-// per compute unit, but 2^22 searches 64 -> 73 us and 2^26 1533 -> 1762 us.)
+// 1.68 ms instead of 1.53). (Slabs left out of LDS, with only their tags there and a found pair
+// read from L2: more parts per compute unit, but 2^22 searches 64 -> 73 us and 2^26 1533 -> 1762.)
 //
 // A run of a tile is a few operations (tile / parts), less than a cache line. Workgroups b,
 // b + 8, b + 16, ... share an XCD, so they take consecutive parts: the lines their runs share
@@ -402,9 +402,9 @@ template <bool KO> constexpr uint32_t kTagWords = KO ? 16u : 8u;
 // queue in LDS, not in registers: eight searches a thread in registers left three wavefronts per
 // SIMD where this form runs six, and took 62 us where it takes 37: 2^22 searches, 2^22 keys.)
 // Lists longer than one slab are taken level by level: while many searches still run, the next
-// slab of every list that has one replaces its row; a wavefront with few left walks their lists
-// itself, one per half wavefront. A thread keeps the searches it has not answered as bits, search tid + i * threads
-// of the queue in bit i.
+// slab of every list with an open one replaces its row; a wavefront with few left walks their
+// lists itself, one per half wavefront. A thread keeps the searches it has not answered as bits,
+// search tid + i * threads of the queue in bit i.
 template <bool KO, int NW>
 __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 {
@@ -596,8 +596,8 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
             if (tid == 0)
                 sh[0] = 0;
             __syncthreads();
-            // the next slab of every list with an open search replaces its row (a list without a next
-            // slab has none)
+            // the next slab of every list with an open search replaces its row (a list without a
+            // next slab has none)
             fresh = true;
             for (uint32_t r0 = wv * 2; r0 < nb; r0 += NW * 2 * kRowLoads) {
                 uint32_t has = 0;
@@ -632,9 +632,9 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
     }
 }
 
-// Inserts of one part, on a unique-key pair table (REPLACE). They are gathered by bucket in LDS, and
-// half a wavefront per slab commits them to the table: one that finds its key gives the slot its
-// value (status 2), another takes the next empty slot (status 1).
+// Inserts of one part, on a unique-key pair table (REPLACE). They are gathered by bucket in LDS,
+// and half a wavefront per slab commits them to the table: one that finds its key gives the slot
+// its value (status 2), another takes the next empty slot (status 1).
 //
 //   new pairs    the first empty slot is swapped to kLockPair, the pairs of the slots after it
 //                are stored in one piece, and the pair of the locked slot is stored last. Slots
@@ -669,8 +669,8 @@ __global__ __launch_bounds__(NW * 64) void probe_kernel(View T, Bulk A)
 // look through LDS per insert, whatever the length of its run. (Comparing the groups of each key in
 // the commit, and leaving what had no place in line to the plain kernel, took the kernel 31.7 us
 // where this takes 21.1 with every key twice, 2^18 in 40,960 buckets; 92 us and 86 more in the
-// plain kernel where this takes 71 and 9 with Zipf(0.8) keys, 2^18 in 21,845; and 71.8 us where this
-// takes 73.8 with distinct keys, 2^22 in 217,000.)
+// plain kernel where this takes 71 and 9 with Zipf(0.8) keys, 2^18 in 21,845; and 71.8 us where
+// this takes 73.8 with distinct keys, 2^22 in 217,000.)
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void insert_kernel(View T, Bulk A)
 {
@@ -1002,8 +1002,8 @@ __global__ __launch_bounds__(kBlock) void later_kernel(View T, Bulk A, uint32_t 
         c.key = in ? A.key[pos] : kEmpty;
         c.val = in ? A.val[pos] : 0u;
         c.op = kInsert;
-        run_chunk<kInsert, false, false, NQ, true>(T, al, cnt, lds[wl_], c, nullptr, A.flag, pos, count,
-                                             0u);
+        run_chunk<kInsert, false, false, NQ, true>(T, al, cnt, lds[wl_], c, nullptr, A.flag, pos,
+                                                   count, 0u);
     }
 }
 

@@ -51,6 +51,7 @@ struct BulkPlan {
 // 32-bit words of one tile's part starts: two 16-bit ones each, and the end of the last.
 constexpr uint32_t split_row_words(uint32_t parts) { return parts / 2 + 1; }
 
+// The calls that have a bulk form (bulk_pays, below, has those for which it is the faster one):
 constexpr uint64_t kBulkSearches = 1u << 21, kBulkInserts = 1u << 17; // the smallest batches
 constexpr uint32_t kBulkCached = 1u << 15;  // base slabs that the L2s hold: 2^21 searches of them
 constexpr uint64_t kBulkCachedSearches = 3u << 20; // take 42 us plain / 46, 2^22 85 / 65
@@ -103,7 +104,7 @@ inline bool bulk_plan(const BulkCall &c, BulkPlan *P)
     // More parts until one fits the LDS beside its queue; where that is not enough, a queue
     // shorter than a part, which is then taken in pieces. (Calls that went the plain way while a
     // part had to fit as it was: 2^26 searches at 16 per bucket 3.01 -> 1.49 ms, of keys alone at
-    // 38 2.48 -> 1.40; 2^26 inserts at 16 per bucket 4.43 -> 2.14 ms, 3 * 2^24 at 9.6 3.49 -> 2.09.)
+    // 38 2.48 -> 1.40; 2^26 inserts at 16 per bucket 4.43 -> 2.14, 3 * 2^24 at 9.6 3.49 -> 2.09.)
     for (;; parts += cus) {
         A.span = (uint32_t)((B + parts - 1) / parts);
         A.parts = (B + A.span - 1) / A.span;

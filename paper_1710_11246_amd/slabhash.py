@@ -10,7 +10,6 @@ uint32 support); ops, statuses and found flags are torch.uint8.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes
 import os
 import re
@@ -183,17 +182,16 @@ def _stream(stream) -> int:
     return int(stream)
 
 
-@contextlib.contextmanager
-def _outside_captures():
-    """Lets this thread take device memory while a stream is being captured, by this thread or by
-    another one. A device allocation is refused meanwhile, and ends the capture, unless the calling
-    thread's capture mode is relaxed (2): memory taken here is no part of any capture."""
+def _outside_captures(take):
+    """take(), which takes device memory, while a stream may be being captured, by this thread or
+    by another one. A device allocation is refused meanwhile, and ends the capture, unless the
+    calling thread's capture mode is relaxed (2): memory taken here is no part of any capture."""
     mode = ctypes.c_int(2)
     exchange = lib().hipThreadExchangeStreamCaptureMode
     if exchange(ctypes.byref(mode)) != 0:
         raise RuntimeError("hipThreadExchangeStreamCaptureMode failed")
     try:
-        yield
+        return take()
     finally:
         exchange(ctypes.byref(mode))
 
@@ -215,7 +213,8 @@ def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     stream that the call runs on, so that it returns to that stream's pool when the call has
     been enqueued. A stream that torch does not own or that is being captured, and a device
     without room, take the plain form. (The size comes first: a call without a bulk form pays for
-    one call into the library and for no Stream object.)"""
+    one call into the library. Neither such a call nor one on the current stream builds a Stream
+    object, which with the switch to it takes 9 us of the host.)"""
     n = keys.numel()
     if n < _BULK_MIN[kind]:
         return None
@@ -223,13 +222,16 @@ def _bulk_work(t, kind: int, keys: torch.Tensor, stream):
     nbytes = lib().sh_bulk_choice(t, kind, n, raw)
     if nbytes == 0:
         return None
-    if stream is None or raw == _current_stream():
-        stream = torch.cuda.current_stream()
-    elif type(stream) is not torch.cuda.Stream:
-        return None
+    def take():
+        return torch.empty(nbytes, dtype=torch.uint8, device=keys.device)
+
     try:
-        with torch.cuda.stream(stream), _outside_captures():
-            return torch.empty(nbytes, dtype=torch.uint8, device=keys.device)
+        if stream is None or raw == _current_stream():
+            return _outside_captures(take)
+        if type(stream) is not torch.cuda.Stream:
+            return None
+        with torch.cuda.stream(stream):
+            return _outside_captures(take)
     except torch.cuda.OutOfMemoryError:
         return None
 
