@@ -264,10 +264,10 @@ sh_status_t sh_search(sh_table_t *t, const uint32_t *d_keys, uint64_t n, uint32_
    in pieces of 2^26.
    sh_bulk_choice is sh_bulk_bytes where the bulk form is also the faster one whatever the batch's
    keys are, and 0 elsewhere: searches from 3.5 * 2^20 and ten per bucket (16 and 64 where the lists
-   may be longer than one slab and than two), inserts into an empty table from 3 * 2^17 (from 2^17
-   with ten per bucket), and inserts beside what a table holds from 2^20 and twelve per bucket. What a
-   table holds is counted by the calls: it is unknown in a table of a multi-table object, and a
-   graph's replays are not in it. */
+   may be longer than one slab and than two), inserts into an empty table from 2^17, 2^18 and
+   3 * 2^17 with 15, ten and six per bucket, and inserts beside what a table holds from 2^20 and
+   twelve per bucket. What a table holds is counted by the calls: it is unknown in a table of a
+   multi-table object, and a graph's replays are not in it. */
 size_t sh_bulk_bytes(const sh_table_t *t, int kind, uint64_t n, void *stream);
 size_t sh_bulk_choice(const sh_table_t *t, int kind, uint64_t n, void *stream);
 sh_status_t sh_search_bulk(sh_table_t *t, const uint32_t *d_keys, uint64_t n,

@@ -153,7 +153,7 @@ inline bool bulk_plan(const BulkCall &c, BulkPlan *P)
 
 // Whether the bulk form is the faster one for the call, whatever its keys: distinct, repeated or
 // popular, present or absent. Each line lies where the slowest distribution measured is level with
-// the plain form (us, plain / bulk; Zipf(0.8) and Zipf(1.1) ranks; "half" with half of them absent):
+// the plain form (us, plain / bulk; Zipf(0.8) and Zipf(1.1) ranks; "half": half of them absent):
 //
 //   searches   the plain form finds popular keys in the caches, and three launches instead of one
 //              cost 10 us: 2.5 * 2^20 at 10 per bucket uniform 101 / 74 but Zipf(1.1) 74 / 80, half
@@ -163,9 +163,13 @@ inline bool bulk_plan(const BulkCall &c, BulkPlan *P)
 //              per bucket 2^22 at 10 197 / 148 but Zipf(0.8) 156 / 175, at 16 189 / 115, 152 / 145;
 //              with 150, Zipf(1.1) at 16 190 / 222 (uniform 462 / 254), with 400 at 64 370 / 383.
 //              So 16 per bucket, and 64, of tables that may hold that much.
-//   inserts    into an empty table, every key once / every key twice: 2^17 at 6.1 per bucket 26 / 26
-//              and 22 / 27, at 10 35 / 24 and 26 / 25; 2^18 at 7 33 / 33 and 29 / 35, at 10 37 / 27
-//              and 31 / 29; 3 * 2^17 at 6.1 39 / 33 and 36 / 34. Popular keys gain most.
+//   inserts    into an empty table, every key once, and twice: 2^17 at 6.1 per bucket 26 / 26 and
+//              22 / 27, at 10 35 / 24 and 26 / 25; 2^18 at 7 33 / 33 and 29 / 35, at 10 37 / 27 and
+//              31 / 29; 3 * 2^17 at 6.1 39 / 33 and 36 / 34. Popular keys gain most. The host takes
+//              16 us for such a call, 4 for a plain one: a pass of reset, inserts, search, delete
+//              and search that is waited for takes at 2^17 and 10 per bucket 69 / 79, at 15 79 / 72;
+//              3 * 2^16 at 10, with small searches, 65 / 71; 2^18 at 10 70 / 70. So 15, 10 and 6
+//              per bucket from 2^17, 2^18 and 3 * 2^17 on.
 //              Beside pairs that the table holds, fresh keys / keys that are all present: 2^18 at
 //              12 on 12 held 47 / 30 and 23 / 37 (a plain insert finds such a key and swaps once);
 //              2^20 92 / 55 and 68 / 69; 2^22 at 8 on 12 266 / 215 and 251 / 257, at 12 289 / 182
@@ -178,10 +182,13 @@ inline bool bulk_pays(const BulkCall &c, bool counted)
     const uint64_t slab = c.keys_only ? 62 : 31; // entries
     if (!c.insert) {
         const uint64_t held = c.since_reset;
-        const uint64_t per = !counted || held > 2 * slab * B ? 64 : held > slab * B * 2 / 3 ? 16 : 10;
+        const uint64_t per = !counted || held > 2 * slab * B ? 64
+                             : held > slab * B * 2 / 3       ? 16
+                                                             : 10;
         return c.n >= (7u << 19) && m / per >= B;
     }
     if (c.since_reset == 0)
-        return c.n >= (1u << 17) && m / (c.n < (3u << 17) ? 10 : 6) >= B;
+        return c.n >= (1u << 17) &&
+               m / (c.n < (1u << 18) ? 15 : c.n < (3u << 17) ? 10 : 6) >= B;
     return c.n >= (1u << 20) && m / 12 >= B;
 }

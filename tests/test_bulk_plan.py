@@ -186,9 +186,10 @@ def test_where_searches_pay(pays, kind):
 
 
 def test_where_inserts_pay(pays):
-    """An empty table from 2^17 at ten per bucket and from 3 * 2^17 at six; any other from 2^20 at
-    twelve."""
-    for n, per in ((1 << 17, 10), ((3 << 17) - 1, 10), (3 << 17, 6), (1 << 26, 6)):
+    """An empty table from 2^17 at 15 per bucket, 2^18 at ten and 3 * 2^17 at six; any other from
+    2^20 at twelve."""
+    for n, per in ((1 << 17, 15), ((1 << 18) - 1, 15), (1 << 18, 10), ((3 << 17) - 1, 10),
+                   (3 << 17, 6), (1 << 26, 6)):
         assert pays(n, n // per, "insert") and not pays(n, n // per + 1, "insert")
     assert not pays((1 << 17) - 1, 2000, "insert")
     for held in (1, 100000):
