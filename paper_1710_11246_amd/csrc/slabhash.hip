@@ -921,6 +921,17 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                     // return; at most the 31 slots of this slab. (With duplicates, empty slots
                     // need not be a suffix, so a lost insert re-reads its slab next round.)
                     for (;;) {
+                        // The swap won, or met the lock of a bulk insert, which holds the slab:
+                        // read it again. (One exit for both, since the two words differ in one
+                        // bit: 1000 inserts into 66 buckets take 17.1 us, 16.9 without a lock to
+                        // look for, and 18.0 with an exit for the lock.)
+                        static_assert((kLockPair | (1ull << 32)) == kEmptyPair, "");
+                        if (Locks ? (old | (1ull << 32)) == kEmptyPair : old == kEmptyPair) {
+                            won = !Locks || old == kEmptyPair;
+                            lost = !won;
+                            rs = won ? 1u : rs;
+                            break;
+                        }
                         if ((uint32_t)old == key) { // the same key was inserted: replace it
                             expect = old;
                             old = cas64(slab + cslot, expect, desired);
@@ -932,20 +943,11 @@ __device__ void run_chunk(const View &T, Alloc &al, Counters &cnt, WaveLds &L, C
                             }
                             break;
                         }
-                        // A slab that a bulk insert holds ends the walk as a full one does. (An
-                        // exit of its own took 1000 inserts into 66 buckets 18.0 us instead of 17.4
-                        // (16.8 without a lock to look for): every step of the walk has it.)
-                        cslot = Locks && old == kLockPair ? 31u : cslot + 1;
-                        if (cslot >= 31) {
+                        if (++cslot >= 31) {
                             lost = true; // slab filled up: the next round follows `next`
                             break;
                         }
                         old = cas64(slab + cslot, kEmptyPair, desired);
-                        if (old == kEmptyPair) {
-                            rs = 1u;
-                            won = true;
-                            break;
-                        }
                     }
                 } else {
                     lost = true;
