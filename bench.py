@@ -41,18 +41,18 @@ B_FOR_UTIL = {0.2: 654181, 0.3: 436670, 0.4: 327431, 0.5: 261962, 0.6: 217316, 0
 # Bytes per launch beyond L2 (reads + writes), from rocprofv3 FETCH_SIZE/WRITE_SIZE runs scaled by
 # a 1 GiB device copy; see profiles/slabhash_step_2p22_traffic.md. Valid only for the kernel
 # source they were measured on (source_sha); otherwise reported as null.
-TRAFFIC_SRC_SHA = "f87bfcd2f0d57c57"
+TRAFFIC_SRC_SHA = "e1cfcc24aa612269"
 # Per launch, from rocprofv3 TCC_HIT_sum/TCC_MISS_sum and TCC_ATOMIC_sum/TCC_EA0_ATOMIC_sum runs
 # of the same source (profiles/slabhash_step_2p22_l2.md): (L2 hit rate, atomics, atomics that
 # reached memory).
-L2_STATS = {"build": (0.3684, 4693064, 4693064), "search_hit": (0.0938, 0, 0),
-            "search_miss": (0.0938, 0, 0), "mixed": (0.3149, 26728, 26728),
-            "reset": (0.5024, 0, 0)}
+L2_STATS = {"build": (0.5775, 223652, 223652), "search_hit": (0.6287, 0, 0),
+            "search_miss": (0.6287, 0, 0), "mixed": (0.3110, 26736, 26736),
+            "reset": (0.5031, 0, 0)}
 # The same for the 2^26-key table of measure_hbm_resident (profiles/slabhash_hbm_2p26_traffic.md).
-HBM_TRAFFIC_BYTES = {"build": 22295350709, "search_hit": 17763213803,
-                     "search_miss": 17763213803}
-TRAFFIC_BYTES = {"build": 1349499276, "search_hit": 1039525491, "search_miss": 1039525491,
-                 "mixed": 19521621, "reset": 56247443}
+HBM_TRAFFIC_BYTES = {"build": 4781137994, "search_hit": 3428275013,
+                     "search_miss": 3428275013}
+TRAFFIC_BYTES = {"build": 247810691, "search_hit": 189472756, "search_miss": 189472756,
+                 "mixed": 19512605, "reset": 56256808}
 
 
 def source_sha() -> str:

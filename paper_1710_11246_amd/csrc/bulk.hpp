@@ -14,9 +14,9 @@
 //
 //                     plain   bulk   of it: split   probe / insert   later   merge
 //   2^22 searches       149     67             16               42               9
-//   2^26 searches      2890   1440            209             1070             167
-//   2^22 inserts        239    111             21               74      11       5
-//   2^26 inserts       4260   2010            296             1650      19      59
+//   2^26 searches      2890   1440            207             1070             167
+//   2^22 inserts        239    110             21               73      11       5
+//   2^26 inserts       4260   2060            298             1680      19      60
 //
 // The plain form reads 256 bytes at random per operation, and an insert swaps 8. Split and merge
 // are bound by memory at 2^26 (split moves 11 bytes per search and 18 per insert: 3.7 and 4.1 TB/s;
